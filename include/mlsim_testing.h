@@ -33,6 +33,8 @@ enum {
   SIM_TEST_CP_GLOBAL = 5,     /* value 0/1: the max-plus sweeps' value slots in global scratch (1) even
                                  when LDS holds them (static-order replays created afterwards too) */
   SIM_TEST_RF_GLOBAL = 6,     /* value 0/1: the event kernel's resource times in global scratch (1) */
+  SIM_TEST_NO_MERGE = 8,      /* value 0/1: the event list (1) even when the graph has a merge program; pins
+                                 1, 3, 4 and 6 imply it */
   SIM_TEST_SHARE_KEY_ID = 7   /* value 0/1: the sharing replay's ready-op key words hold only the op id
                                  (1), as for graphs whose ids and resources do not fit 32 bits together */
 };
@@ -86,6 +88,26 @@ int sim_testing_sweep_table(int32_t n_ops, int32_t n_res, const int64_t *succ_pt
 int sim_testing_join_slots(int32_t n_ops, int32_t n_res, const int64_t *succ_ptr,
                            const int32_t *succ_idx, const int32_t *op_res, const int32_t *prio,
                            int32_t *slot_of, int32_t *n_slots);
+
+/*
+ * The merge program the library builds for a graph, on the host only, so that
+ * a test can interpret it and compare the result with an independent replay.
+ * The graph arguments are those of sim_graph_create; device_model: the program
+ * of calls with gaps or delays.  Outputs (host): head: {instructions, deferred entries, deferred chains, slots, first slot of the
+ * chains' ready times, zero slot, infinity slot, slot nobody reads, 0, 1}, or
+ * ten zeros when the graph has no program; then, when the arrays are large
+ * enough (else SIM_E_LIMIT), ins [][13]: {kind, row, resource, out slot, four
+ * operand slots, first chain of the cluster, one past its last, deferred
+ * index, id, 1 when the ready time is the resource's free time} with kind 0 visit, 1 max, 2 release, 3 load, 4 force, 5 drain;
+ * def [][4]: {row, id, chain, partner (the deferred index it releases when it
+ * runs, whose duration a load hands over; -1: none)}; chain
+ * [][2]: {first deferred index, resource}.  Ids are ranks of (priority, id).
+ * Returns SIM_OK or the argument errors of sim_graph_create.
+ */
+int sim_testing_merge_program(int32_t n_ops, int32_t n_res, const int64_t *succ_ptr,
+                              const int32_t *succ_idx, const int32_t *op_res, const int32_t *prio,
+                              int32_t device_model, int32_t head[10], int32_t *ins, int64_t ins_cap, int32_t *def,
+                              int64_t def_cap, int32_t *chain, int64_t chain_cap);
 
 #ifdef __cplusplus
 }

@@ -29,14 +29,14 @@ SIM_ALGO_AUTO, SIM_ALGO_EVENT, SIM_ALGO_SWEEP = 0, 1, 2
 ALGOS = {"auto": SIM_ALGO_AUTO, "event": SIM_ALGO_EVENT, "sweep": SIM_ALGO_SWEEP}
 #: kernel-variant pins of the testing entry point (include/mlsim_testing.h)
 TEST_VARIANTS = {"auto": 0, "ev_lds_groups": 1, "ev_blocks_cap": 3, "ev_reg": 4, "cp_global": 5,
-                 "rf_global": 6, "share_key_id": 7}
+                 "rf_global": 6, "share_key_id": 7, "no_merge": 8}
 
 EXPORTS = ("sim_graph_create", "sim_graph_destroy", "sim_run_batch", "sim_critical_path",
            "sim_strerror", "sim_graph_info", "sim_testing_replan", "sim_static_create",
            "sim_static_destroy", "sim_static_run", "sim_attribute", "sim_generate", "sim_run_generated",
            "sim_critical_path_generated", "sim_run_batch_gap", "sim_static_run_generated",
            "sim_run_batch_dev", "sim_run_batch_share", "sim_run_batch_noalloc", "sim_testing_sweep_table",
-           "sim_testing_join_slots")
+           "sim_testing_join_slots", "sim_testing_merge_program")
 
 #: generator limits (include/mlsim.h): largest base duration, noise bound
 SIM_GEN_BASE_MAX, SIM_GEN_NOISE_MAX = 1 << 24, 1 << 20
@@ -113,6 +113,8 @@ def _load():
     L.sim_testing_sweep_table.restype = ctypes.c_int
     L.sim_testing_join_slots.argtypes = [I32, I32, P, P, P, P, P, P]
     L.sim_testing_join_slots.restype = ctypes.c_int
+    L.sim_testing_merge_program.argtypes = [I32, I32, P, P, P, P, I32, P, P, I64, P, I64, P, I64]
+    L.sim_testing_merge_program.restype = ctypes.c_int
     _lib = L
     return L
 
@@ -174,6 +176,29 @@ def join_slots(succ_ptr, succ_idx, op_res, n_res: int, prio=None):
     if rc != SIM_OK:
         raise SimError(rc, "sim_testing_join_slots")
     return slot_of[:n].copy(), n_slots.value
+
+
+def merge_program(succ_ptr, succ_idx, op_res, n_res: int, prio=None, device_model: bool = False):
+    """The merge program the library builds for a graph, on the host only
+    (sim_testing_merge_program), or None: ``(head, ins int32 [n, 13], def
+    int32 [m, 4], chain int32 [c, 2])`` as described there."""
+    ptr, idx, res, pr = _host(succ_ptr, np.int64), _host(succ_idx, np.int32), _host(op_res, np.int32), _host(prio, np.int32)
+    n = int(ptr.size - 1)
+    if res.size != n or (pr is not None and pr.size != n):
+        raise ValueError("op_res and prio need one entry per op")
+    head = np.zeros(10, np.int32)
+    out = [np.zeros((0, k), np.int32) for k in (13, 4, 2)]
+    for _ in range(2):  # sizes first, then the arrays
+        rc = _load().sim_testing_merge_program(n, int(n_res), _hptr(ptr), _hptr(idx), _hptr(res), _hptr(pr),
+                                               int(device_model), _hptr(head), *[x for a in out for x in (_hptr(a) if a.size else None, a.shape[0])])
+        if rc not in (SIM_OK, SIM_E_LIMIT):
+            raise SimError(rc, "sim_testing_merge_program")
+        if not head[9]:
+            return None
+        if rc == SIM_OK and out[0].size:
+            break
+        out = [np.zeros((int(head[i]), k), np.int32) for i, k in enumerate((13, 4, 2))]
+    return (head, *out)
 
 
 def _host(a, dt):

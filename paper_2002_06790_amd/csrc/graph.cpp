@@ -39,6 +39,8 @@ struct Compiled {
   std::vector<CpRec> cp;
   std::vector<int32_t> jslot;    // [J] join state slot of each join (the event kernel's join index)
   std::vector<int32_t> join_of;  // [n] the join a compact op waits on (its own or its barrier's), -1
+  MergeProgram merge, merge_dev;  // when has_merge: without and with a device model
+  bool has_merge = false;
   int32_t J = 0, JS = 0, heap_cap = 0, cp_slots = 0, cp_n = 0, max_indeg = 0, levels = 0, barriers = 0;
   int64_t m = 0;
 };
@@ -622,6 +624,14 @@ int compile(int32_t n, int32_t R, const int64_t *succ_ptr, const int32_t *succ_i
 
   C.heap_cap = n ? std::max(1, min_path_cover(n, cs)) : 0;
 
+  {
+    std::vector<int32_t> cres(n);
+    for (int32_t c = 0; c < n; ++c) cres[c] = op_res[orig_of[c]];
+    C.has_merge = build_merge(n, R, cs, cp, cres, orig_of, ctopo, C.merge);
+    C.merge_dev = C.merge;
+    C.has_merge = C.has_merge && merge_slots(C.merge, R, false) && merge_slots(C.merge_dev, R, true);
+  }
+
   // critical-path sweep
   std::vector<int32_t> order;
   build_maxplus(n, cs, cp, {}, {}, orig_of, C.cp, C.cp_pred, C.cp_slots, order, C.cp_n);
@@ -834,6 +844,12 @@ extern "C" int sim_graph_create(int32_t n_ops, int32_t n_res, const int64_t *suc
       ap_ptr[v + 1] = (int32_t)ap.size();
     }
   }
+  std::vector<int32_t> mg_ins, mg_ins_dev, mg_def, mg_chain;
+  if (C.has_merge) {
+    pack_merge(C.merge_dev, mg_ins_dev, mg_def, mg_chain, g->mg_dev);
+    pack_merge(C.merge, mg_ins, mg_def, mg_chain, g->mg);
+  }
+  const size_t o_mgi = take(bytes_of(mg_ins)), o_mgv = take(bytes_of(mg_ins_dev)), o_mgd = take(bytes_of(mg_def)), o_mgc = take(bytes_of(mg_chain));
   const size_t o_app = take(bytes_of(ap_ptr)), o_ap = take(bytes_of(ap)), o_rres = take(bytes_of(row_res));
   if (hipMalloc(&g->dev_mem, off ? off : 256) != hipSuccess) {
     delete g;
@@ -855,6 +871,9 @@ extern "C" int sim_graph_create(int32_t n_ops, int32_t n_res, const int64_t *suc
             put(o_evops, C.ev_ops.data(), bytes_of(C.ev_ops)) && put(o_evsucc, C.ev_succ.data(), bytes_of(C.ev_succ)) &&
             put(o_jinfo, C.jinfo.data(), bytes_of(C.jinfo)) && put(o_evsrc, C.ev_src.data(), bytes_of(C.ev_src)) &&
             put(o_rec16, C.ev_rec16.data(), bytes_of(C.ev_rec16)) &&
+            put(o_mgi, mg_ins.data(), bytes_of(mg_ins)) &&
+            put(o_mgv, mg_ins_dev.data(), bytes_of(mg_ins_dev)) && put(o_mgd, mg_def.data(), bytes_of(mg_def)) &&
+            put(o_mgc, mg_chain.data(), bytes_of(mg_chain)) &&
             put(o_lvl, C.lvl_of.data(), bytes_of(C.lvl_of)) && put(o_levend, C.levend.data(), bytes_of(C.levend));
   if (!ok) {
     (void)hipFree(g->dev_mem);
@@ -902,6 +921,13 @@ extern "C" int sim_graph_create(int32_t n_ops, int32_t n_res, const int64_t *suc
   d.lvl_of = (const int32_t *)(base + o_lvl);
   d.levend = (const int32_t *)(base + o_levend);
   d.n_levels = C.levels;
+
+  for (MergeTable *t : {&g->mg, &g->mg_dev}) {
+    t->R = n_res;
+    t->ins = (const int32_t *)(base + (t == &g->mg ? o_mgi : o_mgv));
+    t->def = (const int32_t *)(base + o_mgd);
+    t->chain = (const int32_t *)(base + o_mgc);
+  }
 
   g->h_orig_of.resize(n_ops);
   for (int32_t c = 0; c < n_ops; ++c) g->h_orig_of[c] = C.ops[c].orig;
@@ -957,6 +983,10 @@ extern "C" int sim_testing_replan(sim_graph *g, int32_t what, int32_t value) {
       if (value < 0 || value > 1) return SIM_E_INVAL;
       v.rf_global = value;
       break;
+    case SIM_TEST_NO_MERGE:
+      if (value < 0 || value > 1) return SIM_E_INVAL;
+      v.no_merge = value;
+      break;
     case SIM_TEST_SHARE_KEY_ID:
       if (value < 0 || value > 1) return SIM_E_INVAL;
       v.share_key_id = value;
@@ -1008,6 +1038,43 @@ extern "C" int sim_testing_join_slots(int32_t n_ops, int32_t n_res, const int64_
       slot_of[C.ops[c].orig] = j < 0 ? -1 : C.jslot[j];
     }
     *n_slots = C.JS;
+  } catch (const std::bad_alloc &) {
+    return SIM_E_NOMEM;
+  }
+  return SIM_OK;
+}
+
+extern "C" int sim_testing_merge_program(int32_t n_ops, int32_t n_res, const int64_t *succ_ptr,
+                                         const int32_t *succ_idx, const int32_t *op_res, const int32_t *prio,
+                                         int32_t device_model, int32_t head[10], int32_t *ins, int64_t ins_cap, int32_t *def,
+                                         int64_t def_cap, int32_t *chain, int64_t chain_cap) {
+  if (!head || ins_cap < 0 || def_cap < 0 || chain_cap < 0) return SIM_E_INVAL;
+  if ((ins_cap > 0 && !ins) || (def_cap > 0 && !def) || (chain_cap > 0 && !chain)) return SIM_E_INVAL;
+  if (int rc = check_graph_args(n_ops, n_res, succ_ptr, succ_idx, op_res)) return rc;
+  try {
+    Compiled C;
+    if (int rc = compile(n_ops, n_res, succ_ptr, succ_idx, op_res, prio, C)) return rc;
+    const MergeProgram &P = device_model ? C.merge_dev : C.merge;
+    std::fill(head, head + 10, 0);
+    if (!C.has_merge) return SIM_OK;
+    const int32_t h[10] = {(int32_t)P.ins.size(), (int32_t)P.def.size(), (int32_t)P.chain.size(), P.slots, P.head_slot,
+                           P.zero_slot, P.inf_slot, P.sink_slot, 0, 1};
+    std::copy(h, h + 10, head);
+    if (h[0] > ins_cap || h[1] > def_cap || h[2] > chain_cap) return SIM_E_LIMIT;
+    for (const MergeIns &I : P.ins) {
+      const MergeCluster k = I.cluster < 0 ? MergeCluster{0, 0, -1} : P.cluster[I.cluster];
+      const int32_t w[13] = {I.kind, I.row, I.res, I.out, I.p[0], I.p[1], I.p[2], I.p[3], k.beg, k.end, I.x, I.id,
+                             I.next && !device_model};
+      ins = std::copy(w, w + 13, ins);
+    }
+    for (const MergeDef &d : P.def) {
+      const int32_t w[4] = {d.row, d.id, d.chain, d.partner};
+      def = std::copy(w, w + 4, def);
+    }
+    for (const MergeChain &c : P.chain) {
+      *chain++ = c.beg;
+      *chain++ = c.res;
+    }
   } catch (const std::bad_alloc &) {
     return SIM_E_NOMEM;
   }

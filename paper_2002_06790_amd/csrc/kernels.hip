@@ -1353,6 +1353,7 @@ int plan_scratch(sim_graph *g) {
   size_t sw_blocks = (size_t)sw_occ;
   if (sw_per_block) sw_blocks = std::min(sw_blocks, std::max<size_t>(1, kSweepBudget / sw_per_block));
 
+  if (int rc = plan_merge(g, cus, heap_g_bytes * ev_grid, P.mg_blocks)) return rc;
   size_t off = 0;
   auto take = [&](size_t b) {
     size_t o = off;
@@ -1416,6 +1417,13 @@ int launch_event_impl(const sim_graph *g, char *base, int64_t n_scen, const int3
                       const DurGen *gen = nullptr, const int32_t *dev = nullptr, bool has_gap = false,
                       bool has_delay = false, const EvScratch *ext = nullptr) {
   const ScratchPlan &P = g->plan;
+  const Variant &V = g->var;
+  // the merge program where the graph has one and no test pins the event list
+  // (its row strides are 32-bit byte counts)
+  if (!place && !ext && ld_dur < (1 << 30) && ld_fin < (1 << 30) && P.mg_blocks[0] && !V.no_merge && V.ev_lds_groups < 0 && !V.ev_blocks_cap && V.ev_reg < 0 &&
+      !V.rf_global)
+    return launch_merge(g, base, n_scen, dur, ld_dur, makespan, finish, ld_fin, status, prev, gen, dev, has_gap,
+                        has_delay, stream);
   EvArgs a{n_scen, dur, ld_dur, place, ld_place, makespan, finish, ld_fin, status,
            ext ? ext->heap : (uint64_t *)(base + g->scratch_ev_heap_off), P.ev_heap_stride, P.ev_heap_le,
            ext ? ext->join : (int2 *)(base + g->scratch_ev_join_off),

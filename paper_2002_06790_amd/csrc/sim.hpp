@@ -69,6 +69,68 @@ struct MpTable {
   int32_t bar;    // 1 when some records are barrier nodes
 };
 
+// The merge program of a graph (merge.cpp): instructions run in order by
+// every scenario of a wavefront.  A visit runs an op, after the deferred ops of
+// its cluster with smaller keys; max takes the maximum of its operands; release
+// hands a deferred op its ready time (the maximum of the operands) and its
+// duration, after a load has handed over its partner's duration; force runs a
+// cluster's deferred ops up to one of them and writes its arrival; drain runs
+// the rest of them.
+constexpr int kMgVisit = 0, kMgMax = 1, kMgRelease = 2, kMgLoad = 3, kMgForce = 4, kMgDrain = 5;
+constexpr int32_t kMergeMaxOps = 32768;  // rows, ids and places in 16 bits
+constexpr int32_t kMergeMaxSlots = 512;
+struct MergeIns {
+  int32_t kind, row, res;  // row: the op's (-1: none)
+  int32_t out;             // slot receiving the arrival or the maximum
+  int32_t p[4];            // operand slots (unused: zero_slot)
+  int32_t cluster;         // -1 when its cluster defers no op
+  int32_t x;               // deferred index
+  int32_t id;              // compact id
+  int32_t local;           // visit: every predecessor is on its own resource
+  int32_t next;            // visit: its one predecessor is the op its resource ran last
+};
+struct MergeDef {  // a deferred op
+  int32_t row, id, chain;
+  int32_t partner;  // deferred op released when it runs (-1: none)
+};
+struct MergeChain {
+  int32_t beg, res;  // its ops: len deferred indices from beg on
+  int32_t follow;    // chain of its ops' partners, place by place (-1: none)
+  int32_t len;
+  int32_t lead;      // the chain it follows (-1: none)
+};
+struct MergeCluster {
+  int32_t beg, end;  // its deferred chains
+  int32_t min_slot;  // slot of the smallest first ready time of its chains (-1: no chain)
+};
+struct MergeProgram {
+  std::vector<MergeIns> ins;
+  std::vector<MergeDef> def;
+  std::vector<MergeChain> chain;
+  std::vector<MergeCluster> cluster;
+  // slots: resource r's free time at r; of n chains, chain c's first ready
+  // time at head_slot + c, that op's duration n further, its partner's
+  // another n further; the clusters' least ready times; constants; values
+  int32_t values = 0;  // before merge_slots, out and p hold value numbers below this
+  int32_t slots = 0, head_slot = 0, zero_slot = 0, inf_slot = 0, sink_slot = 0;
+};
+// Device view of a program; no group: none.
+struct MergeTable {
+  int32_t n_group, n_def, n_chain, R, slots, head_slot, zero_slot, inf_slot;
+  int32_t force, aux;    // some instruction is a force; some chain has a follower
+  const int32_t *ins;    // [n_group + padding][4][64] packed instructions (see merge.hip)
+  const int32_t *def;    // [n_def][2] {row, id}
+  const int32_t *chain;  // [n_chain][4] {first deferred index, resource, following chain, leading chain (-1: none)}
+};
+// Value numbers to slots, for calls with or without a device model; false
+// when there are too many.
+bool merge_slots(MergeProgram &P, int32_t R, bool device_model);
+// False when no program is found (then the event list computes the replay).
+// succ, pred, res, row_of and topo by compact id.
+bool build_merge(int32_t n, int32_t R, const std::vector<std::vector<int32_t>> &succ,
+                 const std::vector<std::vector<int32_t>> &pred, const std::vector<int32_t> &res,
+                 const std::vector<int32_t> &row_of, const std::vector<int32_t> &topo, MergeProgram &P);
+
 // Device view of a compiled graph (plain pointers, passed by value).
 struct DevGraph {
   int32_t n, R, J, nsrc;  // n real ops (barriers follow them), J join state slots
@@ -146,6 +208,7 @@ struct ScratchPlan {
   size_t ev_prev_lds_bytes, at_lds_bytes;
   int32_t rf_lds;       // event kernel: resource times in LDS (1) or global scratch (0)
   int32_t ev_last16;    // attribution's last-op table in 16-bit rows (every row below 0xffff)
+  int32_t mg_blocks[4];  // merge kernel: plain, generated, device model, recording predecessors (0: no program)
   // event kernel with the heap's whole third level in LDS (heap_le
   // ev_wide_le), for calls whose tiles all fit these grids (plain, generated
   // durations, device model, recording predecessors; 0: not planned) and
@@ -163,6 +226,7 @@ struct Variant {
   int32_t ev_reg = -1;         // heap root's children in registers (0/1), -1: auto
   int32_t cp_global = 0;       // max-plus value slots in global scratch (1) even when LDS holds them
   int32_t rf_global = 0;       // resource times in global scratch (1) even when LDS holds them
+  int32_t no_merge = 0;        // the event list (1) even when the graph has a merge program
   int32_t share_key_id = 0;    // sharing replay: ready-op key words without the resource (1)
 };
 
@@ -222,6 +286,7 @@ struct sim_graph {
   int32_t row_identity;  // compact id == caller id for every op (no priorities given)
   int device;
   mlsim::DevGraph dg;
+  mlsim::MergeTable mg, mg_dev;  // the merge program without and with a device model
   mlsim::ScratchPlan plan;
   mlsim::Variant var;
   void *dev_mem;          // one allocation holding every graph array
@@ -332,6 +397,14 @@ int noalloc_setup(int device);
 int launch_event_noalloc(const sim_graph *g, int64_t n_scen, const int32_t *dur, int64_t ld_dur,
                          const uint16_t *place, int64_t ld_place, int32_t *makespan, int32_t *finish,
                          int64_t ld_fin, int32_t *status, hipStream_t stream);
+// the merge program's device form, its grids and scratch, and its launch
+// (prev, gen and dev select the kernel; at most one is given)
+void pack_merge(const MergeProgram &P, std::vector<int32_t> &ins, std::vector<int32_t> &def,
+                std::vector<int32_t> &chain, MergeTable &T);
+int plan_merge(const sim_graph *g, int cus, size_t bytes, int32_t (&blocks)[4]);
+int launch_merge(const sim_graph *g, char *scr, int64_t n_scen, const int32_t *dur, int64_t ld_dur, int32_t *makespan,
+                 int32_t *finish, int64_t ld_fin, int32_t *status, int32_t *prev, const DurGen *gen,
+                 const int32_t *dev, bool has_gap, bool has_delay, hipStream_t stream);
 // sizing of persistent grids and LDS, decided once per graph (and again by
 // sim_testing_replan), and the allocation of the graph's scratch sets
 int plan_scratch(sim_graph *g);
