@@ -168,6 +168,43 @@ def test_random_graph_tables(lib):
         check_static(lib, ptr, idx, res, R, np.array(order, np.int32), dur, prio=pr)
 
 
+def many_gradients(k, workers, back, extra):
+    """`workers` devices of k ops each, op i of all of them before transfer i
+    (one link, ops in id order); back: the devices run their ops from the last
+    to the first, so transfer 0 waits for every op.  extra more ops stand alone on
+    devices of their own, 40 a device."""
+    n = workers * k + k + extra
+    succ = [[] for _ in range(n)]
+    for w in range(workers):
+        for i in range(k):
+            succ[w * k + i].append(workers * k + i)
+    ptr = np.zeros(n + 1, np.int64)
+    ptr[1:] = np.cumsum([len(x) for x in succ])
+    res = np.concatenate([np.repeat(np.arange(workers), k), np.full(k, workers),
+                          np.arange(extra) // 40 + workers + 1]).astype(np.int32)
+    order = np.arange(n, dtype=np.int32)
+    if back:
+        order[:workers * k] = order[:workers * k].reshape(workers, k)[:, ::-1].ravel()
+    return ptr, np.array([x for s in succ for x in s], np.int32), res, workers + 1 + extra // 40, order
+
+
+@pytest.mark.parametrize("k,workers,back,extra", [(130, 2, True, 0), (130, 2, False, 0), (60, 3, True, 0),
+                                                  (40, 6, True, 0), (130, 2, True, 40000)])
+def test_static_tables_drop_implied_edges(lib, k, workers, back, extra):
+    """Tables with more live values than LDS holds (128) are built again
+    without the edges that the devices' orders imply: same finish times.
+    (60, 3) lies below that size; with the 40000 ops on 1000 devices looking
+    for implied edges takes more work than it may, and the table keeps them."""
+    ptr, idx, res, R, order = many_gradients(k, workers, back, extra)
+    dur = W.random_durations(res.size, 12, 1, 1000, np.random.default_rng(k + workers))
+    rec, slots = check_static(lib, ptr, idx, res, R, order, dur)
+    edges = rec[:, 2].sum()
+    if back and extra == 0 and k * workers > 200:
+        assert slots <= 8 + 2 * workers and edges <= workers * (k - 1) + k - 1 + workers
+    elif back and extra:
+        assert slots >= k * workers
+
+
 def test_table_errors(lib):
     ptr = np.array([0, 1, 2, 2], np.int64)
     idx = np.array([1, 2], np.int32)
