@@ -759,6 +759,27 @@ bool build_maxplus(int32_t n, const std::vector<std::vector<int32_t>> &succ,
   return true;
 }
 
+void link_maxplus(std::vector<CpRec> &rec, const std::vector<int32_t> &plist, int32_t slots, int32_t n_sweep) {
+  if (n_sweep == 0) return;
+  const int32_t zslot = slots - 2;
+  for (int32_t k = 0; k < n_sweep; ++k) {
+    CpRec &r = rec[k];
+    const int32_t list = r.npred > 4 ? r.npred - 4 : 0;
+    if (list) {
+      for (int e = 0; e < 4; ++e) r.p[e] = plist[r.pbeg + e];
+      r.pbeg += 4;
+    }
+    r.npred = 2 * list;
+  }
+  // the last record has no successors: its copies write the sink slot, and
+  // find all their inputs in slots, since the record before the first copy is
+  // the last record itself
+  std::fill(rec.begin() + n_sweep, rec.end(), rec[n_sweep - 1]);
+  for (int32_t k = 1; k < n_sweep; ++k)
+    for (int e = 0; e < 4; ++e)
+      if (rec[k].p[e] == rec[k - 1].slot) rec[k].p[e] = zslot, rec[k].npred |= 1;
+}
+
 }  // namespace mlsim
 
 
@@ -844,6 +865,7 @@ extern "C" int sim_graph_create(int32_t n_ops, int32_t n_res, const int64_t *suc
       ap_ptr[v + 1] = (int32_t)ap.size();
     }
   }
+  link_maxplus(C.cp, C.cp_pred, C.cp_slots, C.cp_n);
   std::vector<int32_t> mg_ins, mg_ins_dev, mg_def, mg_chain;
   if (C.has_merge) {
     pack_merge(C.merge_dev, mg_ins_dev, mg_def, mg_chain, g->mg_dev);

@@ -736,6 +736,12 @@ struct MpArgs {
   DurGen gen;         // GEN: durations generated from a knob grid and counter-based noise
 };
 
+// f for each of the numbers U, as compile-time constants
+template <class F, int... U>
+__device__ __forceinline__ void each(std::integer_sequence<int, U...>, F &&f) {
+  (f(std::integral_constant<int, U>{}), ...);
+}
+
 // Max-plus sweep, one scenario per lane: dist(v) = d(v) + max over v's
 // predecessors in the table of their dist, in one topological order shared by
 // the whole wave, in batches of kCpBatch records.  With the DAG's predecessors
@@ -750,7 +756,17 @@ struct MpArgs {
 // t + 4 are in flight.  A batch's records arrive in two registers (lane i
 // holds words i and 64 + i) and stay there until the batch is swept; a field
 // is read by readlane, first the rows (for the batch's loads), later the rest
-// (for its sweep).  MODE: where the value slots live (kCpSlotsLds or
+// (for its sweep).  The sweep itself is a chain of slot reads, and a grid with
+// one wavefront per SIMD has nothing to hide them with: so a record's slots are
+// read before the record ahead of it is finished, whose dist comes from a
+// register instead (link_maxplus marks it), and no record has a branch but for
+// a long list: the table's padding repeats the last record, and lanes past the
+// end repeat the last scenario, with their stores.  A ResNet-50 parameter
+// server (8 workers, 4574 ops, 65536 scenarios, static order with finish rows)
+// takes 0.57 ms, 4.2 TB/s, where it took 0.80 ms with the reads, a test for
+// the table's end and a masked store inside each record's step; the critical
+// path of BERT-Large (262144 scenarios, four wavefronts per SIMD) is bound by
+// its loads and stays at 1.39 ms.  MODE: where the value slots live (kCpSlotsLds or
 // kCpSlotsGlobal); OUT: what besides the per-scenario result is written
 // (kMpOutFinish: every op's dist as finish rows; kMpOutDist: every op's dist
 // for one scenario).  GEN: a batch's "rows" are base durations of the lane's
@@ -778,6 +794,8 @@ __global__ __launch_bounds__(kWave) void k_maxplus(MpTable T, MpArgs a) {
     const bool active = s < a.n_scen;
     const int64_t sc = active ? s : a.n_scen - 1;
     const bool want_dist = OUT == kMpOutDist && s == a.dist_scen;
+    const int32_t *dcol = GEN ? nullptr : a.dur + sc;
+    int32_t *fcol = OUT == kMpOutFinish ? a.finish + sc : nullptr;
     const int64_t S = GEN ? a.gen.scen0 + sc : 0;  // global scenario index of the generator
     const int32_t *brow = GEN ? gen_knob_row(a.gen, S) : nullptr;
     const uint32_t s_lo = (uint32_t)S, s_hi = (uint32_t)((uint64_t)S >> 32);
@@ -794,57 +812,65 @@ __global__ __launch_bounds__(kWave) void k_maxplus(MpTable T, MpArgs a) {
     auto load_recs = [&](int t) -> Recs {
       return Recs{recw[(size_t)t * kBatchWords + lane], recw[(size_t)t * kBatchWords + kWave + lane]};
     };
+#define CP_FIELD(r, u, f) __builtin_amdgcn_readlane(((u) * kRecWords + (f)) < kWave ? (r).w0 : (r).w1, ((u) * kRecWords + (f)) & (kWave - 1))
     // rows of one batch (a barrier's row -1 reads row 0, which its sweep ignores)
     auto load_rows = [&](const Recs &r, int32_t (&dv)[kCpBatch]) {
 #pragma unroll
       for (int u = 0; u < kCpBatch; ++u) {
-        const int w = u * kRecWords;  // word of the batch holding the row
-        const int32_t row = __builtin_amdgcn_readlane(w < kWave ? r.w0 : r.w1, w & (kWave - 1));
+        const int32_t row = CP_FIELD(r, u, 0);
         const uint32_t rr = BAR && row < 0 ? 0u : (uint32_t)row;
-        dv[u] = GEN ? brow[rr] : a.dur[(uint64_t)rr * (uint64_t)a.ld_dur + sc];
+        dv[u] = GEN ? brow[rr] : dcol[(uint64_t)rr * (uint64_t)a.ld_dur];
       }
     };
-    auto sweep = [&](int t, const Recs &r, const int32_t (&dv)[kCpBatch]) {
-#define CP_FIELD(u, f) __builtin_amdgcn_readlane(((u) * kRecWords + (f)) < kWave ? r.w0 : r.w1, ((u) * kRecWords + (f)) & (kWave - 1))
+    uint32_t x[4];      // the inputs of the next record but the dist of the one before it
+    uint32_t prev = 0;  // dist of the record before
+    auto fetch = [&](const Recs &r, auto uc) {
+      constexpr int u = decltype(uc)::value;
 #pragma unroll
-      for (int u = 0; u < kCpBatch; ++u) {
-        // padding records (row of op 0, no predecessors, the sink slot) are
-        // harmless to sweep unless they would write op 0's row
-        if (OUT != kMpOutNone && t * kCpBatch + u >= n) break;
-        const int np = CP_FIELD(u, 2);
-        uint32_t best;
-        if (__builtin_expect(np <= 4, 1)) {  // unused entries name the slot that holds 0
-          const uint32_t x0 = sget(CP_FIELD(u, 4));
-          const uint32_t x1 = sget(CP_FIELD(u, 5));
-          const uint32_t x2 = sget(CP_FIELD(u, 6));
-          const uint32_t x3 = sget(CP_FIELD(u, 7));
-          const uint32_t m01 = x0 > x1 ? x0 : x1, m23 = x2 > x3 ? x2 : x3;
-          best = m01 > m23 ? m01 : m23;
-        } else {
-          best = 0;
-          const int pb = CP_FIELD(u, 3);
-          for (int e = 0; e < np; ++e) {
-            const uint32_t x = sget(cp_pred[pb + e]);
-            best = x > best ? x : best;
+      for (int e = 0; e < 4; ++e) x[e] = sget(CP_FIELD(r, u, 4 + e));
+    };
+    // sweeps a batch; x holds its first record's inputs on entry, and those of
+    // the next batch's (records rn) at the end
+    auto sweep = [&](const Recs &r, const Recs &rn, const int32_t (&dv)[kCpBatch]) {
+      auto one = [&](auto uc) {
+        constexpr int u = decltype(uc)::value;
+        const uint32_t x0 = x[0], x1 = x[1], x2 = x[2], x3 = x[3];
+        if constexpr (u + 1 < kCpBatch)
+          fetch(r, std::integral_constant<int, u + 1>{});
+        else
+          fetch(rn, std::integral_constant<int, 0>{});
+        const uint32_t np = (uint32_t)CP_FIELD(r, u, 2);
+        const uint32_t before = prev & (0u - (np & 1u));
+        const uint32_t m01 = x0 > x1 ? x0 : x1, m23 = x2 > x3 ? x2 : x3;
+        const uint32_t m = m01 > m23 ? m01 : m23;
+        uint32_t best = m > before ? m : before;
+        if (__builtin_expect(np > 1, 0)) {
+          const int pb = CP_FIELD(r, u, 3);
+          for (int e = 0; e < (int)(np >> 1); ++e) {
+            const uint32_t y = sget(cp_pred[pb + e]);
+            best = y > best ? y : best;
           }
         }
         // A barrier's row -1 read op 0's durations (row 0, and op 0's noise
         // counter when generated), so dmin sees nothing that op 0 does not;
         // then a barrier adds 0 and writes no row.  No branch: a barrier's
         // dist never exceeds mx, the max of its predecessors' dist.
-        const int32_t row = BAR || GEN || OUT != kMpOutNone ? CP_FIELD(u, 0) : 0;
+        const int32_t row = BAR || GEN || OUT != kMpOutNone ? CP_FIELD(r, u, 0) : 0;
         const int32_t keep = BAR ? ~(row >> 31) : -1;  // all ones for an op, 0 for a barrier
         int32_t d = dv[u];
         if (GEN) d = gen_duration(d, s_lo, s_hi, (uint32_t)(row & keep), a.gen.key0, a.gen.key1, a.gen.noise);
         dmin = d < dmin ? d : dmin;
         const uint32_t dist = best + (uint32_t)(d & keep);
-        sset(CP_FIELD(u, 1), dist);
+        sset(CP_FIELD(r, u, 1), dist);
         mx = dist > mx ? dist : mx;
-        if (OUT == kMpOutFinish && active && keep) a.finish[(int64_t)row * a.ld_fin + s] = (int32_t)dist;
+        prev = dist;
+        // lanes past the end repeat the last scenario: they store its value again
+        if (OUT == kMpOutFinish && keep) fcol[(uint64_t)(uint32_t)row * (uint64_t)a.ld_fin] = (int32_t)dist;
         if (OUT == kMpOutDist && want_dist && keep) a.dist_out[row] = (int32_t)dist;
-      }
-#undef CP_FIELD
+      };
+      each(std::make_integer_sequence<int, kCpBatch>{}, one);
     };
+#undef CP_FIELD
     // One pipeline step: the records of batch t + 3 (loaded during step
     // t - 1, before batch t + 2's rows) give batch t + 3's rows; batch t + 4's
     // records go out; then batch t is swept.  Loads complete in issue order,
@@ -857,7 +883,7 @@ __global__ __launch_bounds__(kWave) void k_maxplus(MpTable T, MpArgs a) {
       const Recs r3 = rx;
       rx = load_recs(t + 4);
       load_rows(r3, ahead3);
-      sweep(t, r0, cur);
+      sweep(r0, r1, cur);
       r0 = r1;
       r1 = r2;
       r2 = r3;
@@ -870,6 +896,7 @@ __global__ __launch_bounds__(kWave) void k_maxplus(MpTable T, MpArgs a) {
     load_rows(r1, db);
     rx = load_recs(3);
     load_rows(r2, dc);
+    fetch(r0, std::integral_constant<int, 0>{});
     for (int t = 0; t < nbat; t += 4) {
       step(t, da, dd);
       if (t + 1 >= nbat) break;

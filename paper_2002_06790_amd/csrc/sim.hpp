@@ -43,9 +43,9 @@ struct OpRec {
 
 // Per position of the critical-path sweep order (32 bytes): an op, or a
 // barrier node standing for a predecessor set that several ops share.  The table is
-// padded with empty records (row 0, no slot, no predecessors) to whole
-// batches of kCpBatch plus kCpBatch * kCpAhead more, so a sweep can read
-// records and rows ahead without bounds checks.
+// padded to whole batches of kCpBatch plus kCpBatch * kCpAhead more, so a sweep
+// can read records and rows ahead without bounds checks.  link_maxplus turns
+// the records into what the kernel reads.
 constexpr int kCpBatch = 16;  // ops per batch of the sweep
 constexpr int kCpAhead = 4;   // batches of records read ahead
 constexpr int kCpSlotsGlobal = 0, kCpSlotsLds = 1;  // where the sweep's value slots live
@@ -383,6 +383,12 @@ bool build_maxplus(int32_t n, const std::vector<std::vector<int32_t>> &succ,
                    const std::vector<int64_t> &tie, const std::vector<int32_t> &row_of,
                    std::vector<CpRec> &rec, std::vector<int32_t> &plist, int32_t &slots,
                    std::vector<int32_t> &order, int32_t &n_sweep);
+// The records as k_maxplus reads them, once they are final: npred becomes
+// 2 * (predecessors in the list at pbeg, 0 when at most 4 in all) + (1 when the
+// record before is a predecessor), p[] the others (with a list, its first
+// four), and the padding copies of the last record, which write its values
+// again.
+void link_maxplus(std::vector<CpRec> &rec, const std::vector<int32_t> &plist, int32_t slots, int32_t n_sweep);
 // The static-order replay's sweep table for `order` (a permutation of the
 // caller's op ids) over a compiled graph's host view: compact predecessor
 // CSR, compact -> caller ids, each caller id's resource.  SIM_E_INVAL for a

@@ -155,6 +155,7 @@ extern "C" int sim_static_create(const sim_graph *g, const int32_t *order, sim_s
   } catch (const std::bad_alloc &) {
     return SIM_E_NOMEM;
   }
+  link_maxplus(rec, plist, slots, n_sweep);
 
   sim_static *st = new (std::nothrow) sim_static();
   if (!st) return SIM_E_NOMEM;

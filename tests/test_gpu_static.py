@@ -171,3 +171,34 @@ def test_static_full_size_sampled(mlsim):
     assert mk[0].item() == emk[0]
     st_obj.close()
     g.close()
+
+
+@pytest.mark.parametrize("n", [1, 2, 15, 16, 17, 33, 80])
+def test_linked_records(mlsim, n):
+    """The sweep takes the dist of the record before from a register and reads
+    the other inputs early; the last batch repeats the last record and the
+    lanes past the end the last scenario.  Chains and long predecessor lists,
+    op counts beside the batch of 16, scenario counts beside the wavefront;
+    columns past the scenarios stay as they were."""
+    rng = np.random.default_rng(n)
+    chain = [[v + 1] if v + 1 < n else [] for v in range(n)]
+    wide = [sorted({n - 1, *(int(x) for x in rng.integers(u + 1, n, size=3))}) if u + 1 < n else [] for u in range(n)]
+    for succ in (chain, wide):
+        ptr = np.zeros(n + 1, np.int64)
+        ptr[1:] = np.cumsum([len(x) for x in succ])
+        idx = np.array([x for s in succ for x in s], np.int32)
+        for S, R in ((1, 1), (63, 3), (64, n), (65, 3), (130, n)):
+            res = (rng.integers(R, size=n) if R < n else np.arange(n)).astype(np.int32)
+            dur = W.random_durations(n, S, 1, 1000, rng)
+            order = np.arange(n, dtype=np.int32)
+            g = mlsim.Graph(ptr, idx, res, R)
+            st = g.static_order(order)
+            fin = torch.full((n, S + 5), -7, dtype=torch.int32, device="cuda")
+            mk, _, status = st.run(dev(dur), finish=fin[:, :S])
+            torch.cuda.synchronize()
+            omk, ofin, _ = oracle.static_run(ptr, idx, res, R, order, dur)
+            assert np.array_equal(mk.cpu().numpy(), omk) and not status.any()
+            assert np.array_equal(fin[:, :S].cpu().numpy(), ofin)
+            assert (fin[:, S:] == -7).all()
+            st.close()
+            g.close()
