@@ -865,6 +865,12 @@ extern "C" int sim_graph_create(int32_t n_ops, int32_t n_res, const int64_t *suc
       ap_ptr[v + 1] = (int32_t)ap.size();
     }
   }
+  std::vector<AtRec> at_rec(n_ops);
+  for (int32_t v = 0; v < n_ops; ++v) {
+    AtRec r{op_res[v], ap_ptr[v + 1] - ap_ptr[v], ap_ptr[v], {-1, -1, -1}, {0, 0}};
+    for (int e = 0; e < kAtInline && e < r.np; ++e) r.p[e] = ap[r.beg + e];
+    at_rec[v] = r;
+  }
   link_maxplus(C.cp, C.cp_pred, C.cp_slots, C.cp_n);
   std::vector<int32_t> mg_ins, mg_ins_dev, mg_def, mg_chain;
   if (C.has_merge) {
@@ -872,7 +878,7 @@ extern "C" int sim_graph_create(int32_t n_ops, int32_t n_res, const int64_t *suc
     pack_merge(C.merge, mg_ins, mg_def, mg_chain, g->mg);
   }
   const size_t o_mgi = take(bytes_of(mg_ins)), o_mgv = take(bytes_of(mg_ins_dev)), o_mgd = take(bytes_of(mg_def)), o_mgc = take(bytes_of(mg_chain));
-  const size_t o_app = take(bytes_of(ap_ptr)), o_ap = take(bytes_of(ap)), o_rres = take(bytes_of(row_res));
+  const size_t o_atr = take(bytes_of(at_rec)), o_ap = take(bytes_of(ap)), o_rres = take(bytes_of(row_res));
   if (hipMalloc(&g->dev_mem, off ? off : 256) != hipSuccess) {
     delete g;
     return SIM_E_NOMEM;
@@ -888,7 +894,7 @@ extern "C" int sim_graph_create(int32_t n_ops, int32_t n_res, const int64_t *suc
             put(o_topo, C.topo.data(), bytes_of(C.topo)) &&
             put(o_wpp, C.wp_ptr.data(), bytes_of(C.wp_ptr)) && put(o_wp, C.wp.data(), bytes_of(C.wp)) &&
             put(o_wsp, C.ws_ptr.data(), bytes_of(C.ws_ptr)) && put(o_ws, C.ws.data(), bytes_of(C.ws)) &&
-            put(o_app, ap_ptr.data(), bytes_of(ap_ptr)) && put(o_ap, ap.data(), bytes_of(ap)) &&
+            put(o_atr, at_rec.data(), bytes_of(at_rec)) && put(o_ap, ap.data(), bytes_of(ap)) &&
             put(o_rres, row_res.data(), bytes_of(row_res)) &&
             put(o_evops, C.ev_ops.data(), bytes_of(C.ev_ops)) && put(o_evsucc, C.ev_succ.data(), bytes_of(C.ev_succ)) &&
             put(o_jinfo, C.jinfo.data(), bytes_of(C.jinfo)) && put(o_evsrc, C.ev_src.data(), bytes_of(C.ev_src)) &&
@@ -925,7 +931,7 @@ extern "C" int sim_graph_create(int32_t n_ops, int32_t n_res, const int64_t *suc
   d.wp = (const int32_t *)(base + o_wp);
   d.ws_ptr = (const int32_t *)(base + o_wsp);
   d.ws = (const int32_t *)(base + o_ws);
-  d.ap_ptr = (const int32_t *)(base + o_app);
+  d.at_rec = (const AtRec *)(base + o_atr);
   d.ap = (const int32_t *)(base + o_ap);
   d.row_res = (const int32_t *)(base + o_rres);
   d.ev_ops = (const OpRec *)(base + o_evops);

@@ -59,6 +59,15 @@ struct CpRec {
                   // cp_slots - 2, which always holds 0
 };
 
+// What a step of the attribution's chain walk reads of an op (32 bytes).
+constexpr int kAtInline = 3;
+struct AtRec {
+  int32_t res, np;        // resource, predecessors
+  int32_t beg;            // the predecessors in the list: ap[beg, beg + np), ascending
+  int32_t p[kAtInline];   // the first of them, then -1
+  int32_t pad[2];
+};
+
 // Device view of a max-plus sweep table (critical path or static-order
 // replay): records in sweep order and the long predecessor lists.
 struct MpTable {
@@ -158,9 +167,9 @@ struct DevGraph {
   const int32_t *wp;
   const int32_t *ws_ptr;  // [n+nb+1]
   const int32_t *ws;
-  // attribution: predecessors by caller id, ascending ([n+1] CSR), and the
-  // resource of each op by caller id
-  const int32_t *ap_ptr;
+  // attribution, by caller id: what a chain step reads of an op, the
+  // predecessor lists (ascending) and the resource of each op
+  const AtRec *at_rec;
   const int32_t *ap;
   const int32_t *row_res;
   // event kernel: ready-list key words (low 32 bits of a key) are
@@ -198,6 +207,7 @@ struct ScratchPlan {
   // attribution: the event kernel with each op's predecessor on its resource
   // (its last-op table beside the resource times), then the chain kernel
   int32_t ev_prev_blocks, at_blocks, at_lds;
+  int32_t at_quad_tiles;  // attribution: tiles up to which four wavefronts take one
   // generated durations: persistent grids of the event and critical-path kernels
   int32_t ev_gen_blocks, cp_gen_blocks;
   int32_t ev_dev_blocks;  // event kernel with a device model (gaps, delays: their table in LDS)

@@ -157,6 +157,34 @@ def test_attr_wide_rows(mlsim):
     check_attr(mlsim, ptr, idx, res, R, dur, path_scen=3)
 
 
+@pytest.mark.parametrize("S,R", [(1, 5), (63, 200), (130, 5), (512 * 64, 5), (512 * 64 + 1, 5), (512 * 64 + 1, 200)])
+@pytest.mark.parametrize("placed", [False, True])
+def test_attr_walks(mlsim, S, R, placed):
+    """Predecessor lists beside the three that a chain step holds, equal
+    finish times (the lowest id counts) and waits for the resource; four
+    lanes a scenario up to two tiles per CU, one above; accumulators in LDS
+    and, from 129 resources, in global memory; op counts that the four
+    wavefronts share unevenly."""
+    rng = np.random.default_rng(S + R)
+    widths = [1, 2, 3, 4, 5, 8, 9]
+    succ, heads = [], []
+    for w in widths:  # w ops, then one that joins them, feeding the next group
+        base = len(succ)
+        for v in heads:
+            succ[v] += range(base, base + w)
+        succ += [[base + w] for _ in range(w)] + [[]]
+        heads = [base + w]
+    n = len(succ)
+    ptr = np.zeros(n + 1, np.int64)
+    ptr[1:] = np.cumsum([len(x) for x in succ])
+    idx = np.array([x for s in succ for x in s], np.int32)
+    dur = rng.integers(1, 4, size=(n, S)).astype(np.int32)  # many equal finish times
+    dur[0, S // 2] = 0 if S > 1 else dur[0, 0]
+    res = rng.integers(R, size=n).astype(np.int32)
+    place = rng.integers(R, size=(n, S)).astype(np.uint16) if placed else None
+    check_attr(mlsim, ptr, idx, res, R, dur, place=place, path_scen=S - 1)
+
+
 def test_attr_status_and_empty(mlsim):
     ptr = np.array([0, 1, 2, 2], np.int64)
     idx = np.array([1, 2], np.int32)
