@@ -57,8 +57,10 @@ struct Builder {
   std::vector<std::vector<int32_t>> of_res;  // chains of each resource
   std::vector<int32_t> ch, pos;              // chain of an op, its place
   // per op and chain, the last op x of the chain with A(x) <= ready(op)
-  // (rdy) and with A(x) < A(op) (arr); -1: none
-  std::vector<int32_t> rdy, arr;
+  // (rdy) and with A(x) < A(op) (arr); -1: none.  Rows by place in the order
+  // the ops are looked at, and made as they are: a graph whose chains are soon
+  // too many pays only for the rows so far.
+  std::vector<int32_t> rdy, arr, row;
 
   Builder(int n_, int R_, const std::vector<std::vector<int32_t>> &s, const std::vector<std::vector<int32_t>> &p,
           const std::vector<int32_t> &r)
@@ -71,18 +73,18 @@ struct Builder {
     for (int c = 0; c < nch; ++c) raise(to[c], from[c]);
   }
   void learn_ready(int v) {
-    int32_t *r = &rdy[(size_t)v * W];
+    int32_t *r = &rdy[(size_t)row[v] * W];
     for (int32_t p : pred[v]) {
-      raise_all(r, &arr[(size_t)p * W]);
+      raise_all(r, &arr[(size_t)row[p] * W]);
       raise(r[ch[p]], p);
     }
   }
   void learn_arrival(int v) {
-    int32_t *a = &arr[(size_t)v * W];
-    raise_all(a, &rdy[(size_t)v * W]);
+    int32_t *a = &arr[(size_t)row[v] * W];
+    raise_all(a, &rdy[(size_t)row[v] * W]);
     if (pos[v] > 0) {
       const int32_t t = chain[ch[v]][pos[v] - 1];
-      raise_all(a, &arr[(size_t)t * W]);
+      raise_all(a, &arr[(size_t)row[t] * W]);
       raise(a[ch[t]], t);
     }
   }
@@ -93,7 +95,7 @@ struct Builder {
     if (pred[z].empty()) return false;
     if (ch[v] >= 0 && ch[v] == ch[z]) return pos[v] < pos[z];
     bool strict = true;
-    const int32_t *r = &rdy[(size_t)z * W];
+    const int32_t *r = &rdy[(size_t)row[z] * W];
     for (int32_t p : pred[v]) {
       const int32_t x = r[ch[p]];
       if (x < 0 || pos[p] > pos[x]) return false;
@@ -135,9 +137,16 @@ struct Builder {
     of_res.assign(R, {});
     ch.assign(n, -1);
     pos.assign(n, 0);
-    rdy.assign((size_t)n * W, -1);
-    arr.assign((size_t)n * W, -1);
+    row.assign(n, -1);
+    rdy.clear();
+    arr.clear();
+    rdy.reserve((size_t)n * W);
+    arr.reserve((size_t)n * W);
+    int32_t rows = 0;
     for (int32_t v : topo) {
+      row[v] = rows++;
+      rdy.resize((size_t)rows * W, -1);
+      arr.resize((size_t)rows * W, -1);
       learn_ready(v);
       if (!place(v)) return false;
       learn_arrival(v);
@@ -153,20 +162,25 @@ struct Builder {
 }  // namespace
 
 namespace {
-bool build(int32_t n, int32_t R, const std::vector<std::vector<int32_t>> &succ,
-                 const std::vector<std::vector<int32_t>> &pred, const std::vector<int32_t> &res,
-                 const std::vector<int32_t> &row_of, const std::vector<int32_t> &topo, bool partners, MergeProgram &P) {
-  P = MergeProgram{};
+// the chains of a graph's ops; false: too many
+bool find_chains(Builder &B, const std::vector<int32_t> &topo) {
+  const int32_t n = B.n;
   if (n < 1 || n > kMergeMaxOps) return false;
-  Builder B(n, R, succ, pred, res);
   // ids are usually a topological order in which one device's ops follow one
   // another, which keeps its long chain whole
   bool ids = true;
   for (int32_t v = 0; v < n && ids; ++v)
-    for (int32_t w : succ[v]) ids = ids && w > v;
+    for (int32_t w : B.succ[v]) ids = ids && w > v;
   std::vector<int32_t> order(topo);
   if (ids) std::iota(order.begin(), order.end(), 0);
-  if (!B.chains(order) && (!ids || !B.chains(topo))) return false;
+  return B.chains(order) || (ids && B.chains(topo));
+}
+
+bool build(const Builder &B, const std::vector<int32_t> &row_of, bool partners, MergeProgram &P) {
+  P = MergeProgram{};
+  const int32_t n = B.n, R = B.R;
+  const std::vector<std::vector<int32_t>> &succ = B.succ, &pred = B.pred;
+  const std::vector<int32_t> &res = B.res;
 
   // clusters: resources with several chains, united where a deferred op feeds
   // another one's; one spine chain each (the longest), and every resource
@@ -488,7 +502,9 @@ bool merge_slots(MergeProgram &P, int32_t R, bool device_model) {
 bool build_merge(int32_t n, int32_t R, const std::vector<std::vector<int32_t>> &succ,
                  const std::vector<std::vector<int32_t>> &pred, const std::vector<int32_t> &res,
                  const std::vector<int32_t> &row_of, const std::vector<int32_t> &topo, MergeProgram &P) {
-  return build(n, R, succ, pred, res, row_of, topo, true, P) || build(n, R, succ, pred, res, row_of, topo, false, P);
+  P = MergeProgram{};
+  Builder B(n, R, succ, pred, res);
+  return find_chains(B, topo) && (build(B, row_of, true, P) || build(B, row_of, false, P));
 }
 
 }  // namespace mlsim
