@@ -844,7 +844,7 @@ extern "C" int sim_graph_create(int32_t n_ops, int32_t n_res, const int64_t *suc
   };
   size_t o_ops = take(bytes_of(C.ops)), o_succ = take(bytes_of(C.succ)),
          o_jneed = take(bytes_of(C.jneed)), o_src = take(bytes_of(C.src)),
-         o_cp = take(bytes_of(C.cp)), o_cpp = take(bytes_of(C.cp_pred)),
+         o_cp = take(bytes_of(C.cp)), o_cpl = take(bytes_of(C.cp)), o_cpp = take(bytes_of(C.cp_pred)),
          o_pp = take(bytes_of(C.pred_ptr)), o_pr = take(bytes_of(C.pred)),
          o_topo = take(bytes_of(C.topo)), o_wpp = take(bytes_of(C.wp_ptr)),
          o_wp = take(bytes_of(C.wp)), o_wsp = take(bytes_of(C.ws_ptr)), o_ws = take(bytes_of(C.ws)),
@@ -871,6 +871,7 @@ extern "C" int sim_graph_create(int32_t n_ops, int32_t n_res, const int64_t *suc
     for (int e = 0; e < kAtInline && e < r.np; ++e) r.p[e] = ap[r.beg + e];
     at_rec[v] = r;
   }
+  const std::vector<CpRec> cp_plain(C.cp);
   link_maxplus(C.cp, C.cp_pred, C.cp_slots, C.cp_n);
   std::vector<int32_t> mg_ins, mg_ins_dev, mg_def, mg_chain;
   if (C.has_merge) {
@@ -889,7 +890,8 @@ extern "C" int sim_graph_create(int32_t n_ops, int32_t n_res, const int64_t *suc
   };
   bool ok = put(o_ops, C.ops.data(), bytes_of(C.ops)) && put(o_succ, C.succ.data(), bytes_of(C.succ)) &&
             put(o_jneed, C.jneed.data(), bytes_of(C.jneed)) && put(o_src, C.src.data(), bytes_of(C.src)) &&
-            put(o_cp, C.cp.data(), bytes_of(C.cp)) && put(o_cpp, C.cp_pred.data(), bytes_of(C.cp_pred)) &&
+            put(o_cp, C.cp.data(), bytes_of(C.cp)) && put(o_cpl, cp_plain.data(), bytes_of(cp_plain)) &&
+            put(o_cpp, C.cp_pred.data(), bytes_of(C.cp_pred)) &&
             put(o_pp, C.pred_ptr.data(), bytes_of(C.pred_ptr)) && put(o_pr, C.pred.data(), bytes_of(C.pred)) &&
             put(o_topo, C.topo.data(), bytes_of(C.topo)) &&
             put(o_wpp, C.wp_ptr.data(), bytes_of(C.wp_ptr)) && put(o_wp, C.wp.data(), bytes_of(C.wp)) &&
@@ -922,6 +924,7 @@ extern "C" int sim_graph_create(int32_t n_ops, int32_t n_res, const int64_t *suc
   d.jneed = (const int32_t *)(base + o_jneed);
   d.src = (const int32_t *)(base + o_src);
   d.cp = (const CpRec *)(base + o_cp);
+  d.cp_plain = (const CpRec *)(base + o_cpl);
   d.cp_pred = (const int32_t *)(base + o_cpp);
   d.pred_ptr = (const int32_t *)(base + o_pp);
   d.pred = (const int32_t *)(base + o_pr);

@@ -765,14 +765,16 @@ __device__ __forceinline__ void each(std::integer_sequence<int, U...>, F &&f) {
 // server (8 workers, 4574 ops, 65536 scenarios, static order with finish rows)
 // takes 0.57 ms, 4.2 TB/s, where it took 0.80 ms with the reads, a test for
 // the table's end and a masked store inside each record's step; the critical
-// path of BERT-Large (262144 scenarios, four wavefronts per SIMD) is bound by
-// its loads and stays at 1.39 ms.  MODE: where the value slots live (kCpSlotsLds or
+// path of BERT-Large takes 0.78 ms where it took 0.91 ms at 65536 scenarios
+// (CARRY).  With four wavefronts per SIMD the loads bound it, and the table as
+// it is built is swept a record at a time (!CARRY; launch_cp has the rule).
+// MODE: where the value slots live (kCpSlotsLds or
 // kCpSlotsGlobal); OUT: what besides the per-scenario result is written
 // (kMpOutFinish: every op's dist as finish rows; kMpOutDist: every op's dist
 // for one scenario).  GEN: a batch's "rows" are base durations of the lane's
 // knob, and the sweep turns them into durations with the counter-based noise
 // of a.gen.  BAR: the table holds barrier records.
-template <int MODE, int OUT, bool GEN, bool BAR>
+template <int MODE, int OUT, bool GEN, bool BAR, bool CARRY>
 __global__ __launch_bounds__(kWave) void k_maxplus(MpTable T, MpArgs a) {
   extern __shared__ uint32_t lds32[];
   const int lane = threadIdx.x;
@@ -819,7 +821,10 @@ __global__ __launch_bounds__(kWave) void k_maxplus(MpTable T, MpArgs a) {
       for (int u = 0; u < kCpBatch; ++u) {
         const int32_t row = CP_FIELD(r, u, 0);
         const uint32_t rr = BAR && row < 0 ? 0u : (uint32_t)row;
-        dv[u] = GEN ? brow[rr] : dcol[(uint64_t)rr * (uint64_t)a.ld_dur];
+        if (!CARRY)
+          dv[u] = GEN ? brow[rr] : a.dur[(uint64_t)rr * (uint64_t)a.ld_dur + sc];
+        else
+          dv[u] = GEN ? brow[rr] : dcol[(uint64_t)rr * (uint64_t)a.ld_dur];
       }
     };
     uint32_t x[4];      // the inputs of the next record but the dist of the one before it
@@ -829,7 +834,40 @@ __global__ __launch_bounds__(kWave) void k_maxplus(MpTable T, MpArgs a) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) x[e] = sget(CP_FIELD(r, u, 4 + e));
     };
-    // sweeps a batch; x holds its first record's inputs on entry, and those of
+    // !CARRY: sweeps batch t, a record at a time
+    auto sweep_plain = [&](int t, const Recs &r, const int32_t (&dv)[kCpBatch]) {
+      auto one = [&](auto uc) {
+        constexpr int u = decltype(uc)::value;
+        // padding records (row of op 0, no predecessors, the sink slot) are
+        // harmless to sweep unless they would write op 0's row
+        if (OUT != kMpOutNone && t * kCpBatch + u >= n) return;
+        const int np = CP_FIELD(r, u, 2);
+        uint32_t best;
+        if (__builtin_expect(np <= 4, 1)) {  // unused entries name the slot that holds 0
+          const uint32_t x0 = sget(CP_FIELD(r, u, 4)), x1 = sget(CP_FIELD(r, u, 5));
+          const uint32_t x2 = sget(CP_FIELD(r, u, 6)), x3 = sget(CP_FIELD(r, u, 7));
+          const uint32_t m01 = x0 > x1 ? x0 : x1, m23 = x2 > x3 ? x2 : x3;
+          best = m01 > m23 ? m01 : m23;
+        } else {
+          best = 0;
+          const int pb = CP_FIELD(r, u, 3);
+          for (int e = 0; e < np; ++e) {
+            const uint32_t y = sget(cp_pred[pb + e]);
+            best = y > best ? y : best;
+          }
+        }
+        const int32_t row = BAR || OUT != kMpOutNone ? CP_FIELD(r, u, 0) : 0;
+        const int32_t keep = BAR ? ~(row >> 31) : -1;  // as below
+        const int32_t d = dv[u];
+        dmin = d < dmin ? d : dmin;
+        const uint32_t dist = best + (uint32_t)(d & keep);
+        sset(CP_FIELD(r, u, 1), dist);
+        mx = dist > mx ? dist : mx;
+        if (OUT == kMpOutDist && want_dist && keep) a.dist_out[row] = (int32_t)dist;
+      };
+      each(std::make_integer_sequence<int, kCpBatch>{}, one);
+    };
+    // CARRY: sweeps a batch; x holds its first record's inputs on entry, and those of
     // the next batch's (records rn) at the end
     auto sweep = [&](const Recs &r, const Recs &rn, const int32_t (&dv)[kCpBatch]) {
       auto one = [&](auto uc) {
@@ -840,9 +878,9 @@ __global__ __launch_bounds__(kWave) void k_maxplus(MpTable T, MpArgs a) {
         else
           fetch(rn, std::integral_constant<int, 0>{});
         const uint32_t np = (uint32_t)CP_FIELD(r, u, 2);
-        const uint32_t before = prev & (0u - (np & 1u));
         const uint32_t m01 = x0 > x1 ? x0 : x1, m23 = x2 > x3 ? x2 : x3;
         const uint32_t m = m01 > m23 ? m01 : m23;
+        const uint32_t before = prev & (0u - (np & 1u));
         uint32_t best = m > before ? m : before;
         if (__builtin_expect(np > 1, 0)) {
           const int pb = CP_FIELD(r, u, 3);
@@ -883,7 +921,10 @@ __global__ __launch_bounds__(kWave) void k_maxplus(MpTable T, MpArgs a) {
       const Recs r3 = rx;
       rx = load_recs(t + 4);
       load_rows(r3, ahead3);
-      sweep(r0, r1, cur);
+      if constexpr (CARRY)
+        sweep(r0, r1, cur);
+      else
+        sweep_plain(t, r0, cur);
       r0 = r1;
       r1 = r2;
       r2 = r3;
@@ -896,7 +937,7 @@ __global__ __launch_bounds__(kWave) void k_maxplus(MpTable T, MpArgs a) {
     load_rows(r1, db);
     rx = load_recs(3);
     load_rows(r2, dc);
-    fetch(r0, std::integral_constant<int, 0>{});
+    if constexpr (CARRY) fetch(r0, std::integral_constant<int, 0>{});
     for (int t = 0; t < nbat; t += 4) {
       step(t, da, dd);
       if (t + 1 >= nbat) break;
@@ -1483,6 +1524,7 @@ int plan_scratch(sim_graph *g) {
                               : occupancy_blocks(k_attr<false, false>, P.at_lds_bytes, cus);
   if (at_occ < 0) return SIM_E_HIP;
   P.at_quad_tiles = 2 * cus;
+  P.cp_carry_blocks = 3 * 4 * cus;  // launch_cp
   P.at_blocks = (int32_t)(P.at_lds ? at_occ
                                    : std::min<size_t>(at_occ, std::max<size_t>(1, kScratchBudget / at_bytes)));
 
@@ -1852,28 +1894,30 @@ namespace {
 using MpKernel = void (*)(MpTable, MpArgs);
 
 template <int M, int O>
-MpKernel mp_kernel_of(bool gen, bool bar) {
-  if (gen) return bar ? k_maxplus<M, O, true, true> : k_maxplus<M, O, true, false>;
-  return bar ? k_maxplus<M, O, false, true> : k_maxplus<M, O, false, false>;
+MpKernel mp_kernel_of(bool gen, bool bar, bool carry) {
+  if (gen) return bar ? k_maxplus<M, O, true, true, true> : k_maxplus<M, O, true, false, true>;
+  if (carry) return bar ? k_maxplus<M, O, false, true, true> : k_maxplus<M, O, false, false, true>;
+  constexpr bool always = O == kMpOutFinish;  // finish rows: linked tables only
+  return bar ? k_maxplus<M, O, false, true, always> : k_maxplus<M, O, false, false, always>;
 }
 
 // the sweep instance for a slot placement, what it writes, generated
 // durations and whether the table holds barrier records
-MpKernel mp_kernel(int mode, int out, bool gen, bool bar) {
+MpKernel mp_kernel(int mode, int out, bool gen, bool bar, bool carry) {
   if (mode == kCpSlotsLds) {
-    if (out == kMpOutFinish) return mp_kernel_of<kCpSlotsLds, kMpOutFinish>(gen, bar);
-    if (out == kMpOutDist) return mp_kernel_of<kCpSlotsLds, kMpOutDist>(gen, bar);
-    return mp_kernel_of<kCpSlotsLds, kMpOutNone>(gen, bar);
+    if (out == kMpOutFinish) return mp_kernel_of<kCpSlotsLds, kMpOutFinish>(gen, bar, carry);
+    if (out == kMpOutDist) return mp_kernel_of<kCpSlotsLds, kMpOutDist>(gen, bar, carry);
+    return mp_kernel_of<kCpSlotsLds, kMpOutNone>(gen, bar, carry);
   }
-  if (out == kMpOutFinish) return mp_kernel_of<kCpSlotsGlobal, kMpOutFinish>(gen, bar);
-  if (out == kMpOutDist) return mp_kernel_of<kCpSlotsGlobal, kMpOutDist>(gen, bar);
-  return mp_kernel_of<kCpSlotsGlobal, kMpOutNone>(gen, bar);
+  if (out == kMpOutFinish) return mp_kernel_of<kCpSlotsGlobal, kMpOutFinish>(gen, bar, carry);
+  if (out == kMpOutDist) return mp_kernel_of<kCpSlotsGlobal, kMpOutDist>(gen, bar, carry);
+  return mp_kernel_of<kCpSlotsGlobal, kMpOutNone>(gen, bar, carry);
 }
 
 }  // namespace
 
 int maxplus_occupancy(int mode, bool fin, size_t lds, int cus, bool gen, bool bar) {
-  return occupancy_blocks(mp_kernel(mode, fin ? kMpOutFinish : kMpOutNone, gen, bar), lds, cus);
+  return occupancy_blocks(mp_kernel(mode, fin ? kMpOutFinish : kMpOutNone, gen, bar, true), lds, cus);
 }
 
 int launch_maxplus(const MpTable &T, int mode, int max_blocks, size_t lds, int64_t n_scen,
@@ -1887,7 +1931,7 @@ int launch_maxplus(const MpTable &T, int mode, int max_blocks, size_t lds, int64
   const dim3 grid((unsigned)std::min<int64_t>(tiles, max_blocks)), blk(kWave);
   const int out_kind = finish ? kMpOutFinish : dist_out ? kMpOutDist : kMpOutNone;
   void *args[] = {&t, &a};
-  if (hipLaunchKernel((const void *)mp_kernel(mode, out_kind, gen != nullptr, T.bar != 0), grid, blk, args, lds,
+  if (hipLaunchKernel((const void *)mp_kernel(mode, out_kind, gen != nullptr, T.bar != 0, T.carry != 0), grid, blk, args, lds,
                       stream) != hipSuccess)
     return SIM_E_HIP;
   return hipGetLastError() == hipSuccess ? SIM_OK : SIM_E_HIP;
@@ -1897,7 +1941,16 @@ int launch_cp(const sim_graph *g, char *scr, int64_t n_scen, const int32_t *dur,
               int32_t *cp_len, int32_t *dist_out, int64_t dist_scen, hipStream_t stream,
               const DurGen *gen) {
   const ScratchPlan &P = g->plan;
-  const MpTable T{g->dg.cp_n, g->dg.cp_slots, g->dg.cp, g->dg.cp_pred, g->dg.cp_n > g->dg.n};
+  // Up to three wavefronts per SIMD the sweep that reads ahead in the linked
+  // table is faster; with four it is bound by the duration rows, and the other
+  // one streams them a little faster.  BERT-Large (16 workers), reading ahead /
+  // not: 779 / 906 us at 65536 scenarios, 900 / 970 at 131072, 1105 / 1138 at
+  // 196608, 1470 / 1370 to 1440 at 262144.  With durations generated it is
+  // always the faster one (4.84 / 4.89 ms at 262144).
+  const int64_t tiles = (n_scen + kWave - 1) / kWave;
+  const bool carry = gen || std::min<int64_t>(tiles, P.cp_blocks) <= P.cp_carry_blocks;
+  const MpTable T{g->dg.cp_n, g->dg.cp_slots, carry ? g->dg.cp : g->dg.cp_plain, g->dg.cp_pred,
+                  g->dg.cp_n > g->dg.n, carry};
   return launch_maxplus(T, P.cp_mode, gen ? P.cp_gen_blocks : P.cp_blocks, P.cp_lds_bytes, n_scen, dur,
                         ld_dur, cp_len, nullptr, nullptr, 0, dist_out, dist_scen,
                         (uint32_t *)(scr + g->scratch_cp_off), stream, gen);

@@ -76,6 +76,7 @@ struct MpTable {
   const CpRec *rec;
   const int32_t *pred;
   int32_t bar;    // 1 when some records are barrier nodes
+  int32_t carry;  // 1 when link_maxplus has run over the records
 };
 
 // The merge program of a graph (merge.cpp): instructions run in order by
@@ -152,6 +153,7 @@ struct DevGraph {
   const int32_t *jneed;   // [joins] predecessors a join waits for
   const int32_t *src;     // [nsrc] compact ids of sources
   const CpRec *cp;        // [round_up(n, kCpBatch) + kCpBatch * kCpAhead]
+  const CpRec *cp_plain;  // the same before link_maxplus
   const int32_t *cp_pred; // predecessor slot lists of the critical-path sweep
   const int32_t *pred_ptr;// [n + 1] compact predecessor CSR (sweep variant)
   const int32_t *pred;    // compact predecessor ids
@@ -207,6 +209,7 @@ struct ScratchPlan {
   // attribution: the event kernel with each op's predecessor on its resource
   // (its last-op table beside the resource times), then the chain kernel
   int32_t ev_prev_blocks, at_blocks, at_lds;
+  int32_t cp_carry_blocks;  // critical path: blocks up to which the linked table is swept
   int32_t at_quad_tiles;  // attribution: tiles up to which four wavefronts take one
   // generated durations: persistent grids of the event and critical-path kernels
   int32_t ev_gen_blocks, cp_gen_blocks;

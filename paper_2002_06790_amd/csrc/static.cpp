@@ -182,7 +182,7 @@ extern "C" int sim_static_create(const sim_graph *g, const int32_t *order, sim_s
     sim_static_destroy(st);
     return SIM_E_HIP;
   }
-  st->tab = MpTable{n_sweep, slots, (const CpRec *)base, (const int32_t *)(base + pl_off), n_sweep > n};
+  st->tab = MpTable{n_sweep, slots, (const CpRec *)base, (const int32_t *)(base + pl_off), n_sweep > n, 1};
   // value slots in LDS when they fit, else in global scratch for the grid
   const size_t slot_bytes = (size_t)slots * kWave * 4;
   st->mode = slot_bytes <= kSlotsLdsMax && !g->var.cp_global ? kCpSlotsLds : kCpSlotsGlobal;

@@ -150,3 +150,32 @@ def test_generated_barrier_table(mlsim):
     assert np.array_equal(cp.cpu().numpy(), ocp)
     assert set(np.nonzero(ocp < 0)[0] // kb % 3) == {1}
     g.close()
+
+
+@pytest.mark.parametrize("n", [1, 16, 17, 50])
+@pytest.mark.parametrize("tiles", [3072, 3073])
+def test_critical_path_linked_and_plain(mlsim, n, tiles):
+    """Up to three wavefronts per SIMD (3072 tiles of 64 scenarios on 256 CUs)
+    the critical path sweeps the linked table, above that the plain one: chains,
+    lists of more than four predecessors and sets that several ops share, with
+    a ragged last tile, a bad duration and one scenario's path."""
+    rng = np.random.default_rng(n)
+    chain = [[v + 1] if v + 1 < n else [] for v in range(n)]
+    many = [list(range(7, n)) if u < 7 else [] for u in range(n)]  # ops 0 to 6 before all others
+    wide = [sorted({n - 1, *(int(x) for x in rng.integers(u + 1, n, size=3))}) if u + 1 < n else [] for u in range(n)]
+    S = tiles * 64 - 3
+    dur = rng.integers(1, 1000, size=(n, S), dtype=np.int32)
+    dur[0, 5] = 0
+    for succ in (chain, many, wide):
+        ptr = np.zeros(n + 1, np.int64)
+        ptr[1:] = np.cumsum([len(x) for x in succ])
+        idx = np.array([x for s in succ for x in s], np.int32)
+        g = mlsim.Graph(ptr, idx, np.zeros(n, np.int32), 1)
+        d = torch.from_numpy(dur).cuda()
+        cp, _ = g.critical_path(d)
+        cp2, path = g.critical_path(d, path_scen=S - 1)
+        torch.cuda.synchronize()
+        ocp, opath = oracle.critical_path(ptr, idx, n, dur, path_scen=S - 1)
+        assert np.array_equal(cp.cpu().numpy(), ocp) and np.array_equal(cp2.cpu().numpy(), ocp)
+        assert list(path) == list(opath)
+        g.close()
