@@ -528,12 +528,11 @@ def main():
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                      "frac": achieved / PEAK_HBM_GBS, "traffic": traffic,
                      "traffic_unit": "HBM bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, scaled)",
-                     "kernel": "k_event (sim_run_batch)",
+                     "kernel": "k_merge (sim_run_batch)",
                      "bytes_per_launch": alg_bytes,
-                     "limiter": "the CUs' vector memory address path: every step issues about 6.4 "
-                                "lane-divergent loads and stores (record, duration, heap levels beyond LDS, "
-                                "join state, finish bursts) and the TA units are busy about 70% of the launch "
-                                "(profiles/); the roofline axis is HBM bytes, which the kernel does not reach"},
+                     "limiter": "the instruction stream of at most four wavefronts per SIMD, and the deferred "
+                                "ops, whose accesses differ between lanes; the roofline axis is HBM bytes, which "
+                                "the kernel does not reach"},
         "cpu_baseline": cpu,
         "parity": parity,
         "per_config": per_config,
