@@ -312,8 +312,10 @@ bool build(const Builder &B, const std::vector<int32_t> &row_of, bool partners, 
       if (!known[p]) return false;
     return true;
   };
-  // an open op that only another deferred op can release comes after that one
-  auto follows = [&](int32_t v) { return leader[v] >= 0 && state[leader[v]] != kVisited && !known[leader[v]]; };
+  // an open op that only another open one can release comes after that one
+  // (once that one has been released, or is itself released by a leader's run,
+  // it may have run already)
+  auto follows = [&](int32_t v) { return leader[v] >= 0 && state[leader[v]] == kOpen; };
   int64_t budget = kWorkMax;  // ops looked at; a graph that needs more gets no program
   auto first_open = [&](int c) -> int32_t {  // -1: none
     const auto &C = B.chain[c];

@@ -46,10 +46,11 @@ def test_parameter_server_workloads(make, workers):
           gap=rng.integers(0, 50, w.n_res).astype(np.int32), delay=rng.integers(0, 90, w.n_res).astype(np.int32))
 
 
-def ps_graph(rng):
+def ps_graph(rng, hops=1, extra=False):
     """A few workers whose chains feed links, aggregates and updates, some of
-    them sharing a resource, with shuffled ids."""
-    workers, layers, links, per = (int(rng.integers(1, h)) for h in (4, 5, 4, 4))
+    them sharing a resource, with shuffled ids.  Some pulls take up to ``hops``
+    transfers in a row; ``extra`` adds and drops a few edges."""
+    workers, layers, links, per = (int(rng.integers(1, h)) for h in (4, 5, 3 + hops, 4))
     links -= 1
     R = workers * (1 + links) + 1
     ops, edges = [], []
@@ -77,11 +78,17 @@ def ps_graph(rng):
     for w in range(workers):
         for layer in range(layers):
             pull = op(link(w, 1), *([agg[layer]] if server else [push[v, layer] for v in range(workers)]))
+            for k in range(int(rng.integers(0, hops)) if hops > 1 else 0):
+                pull = op(link(w, 2 + k), pull)
             if rng.random() < 0.8:
                 u = op(w, pull)
                 if rng.random() < 0.2:
                     op(w, u)
     n = len(ops)
+    if extra:
+        if rng.random() < 0.4:
+            edges = [e for e in edges if rng.random() > 0.08]
+        edges += [tuple(sorted(rng.choice(n, 2, replace=False))) for _ in range(int(rng.integers(0, 4))) if n > 1]
     perm = rng.permutation(n) if rng.random() < 0.5 else np.arange(n)
     e = np.array(sorted((perm[a], perm[b]) for a, b in edges), np.int64).reshape(-1, 2)
     ptr = np.concatenate([[0], np.cumsum(np.bincount(e[:, 0], minlength=n))]).astype(np.int64)
@@ -108,3 +115,39 @@ def test_random_graphs(family):
     assert all(seen[k] for k in (VISIT, RELEASE, FORCE)), seen
     if family == "workers":
         assert seen[LOAD], seen
+
+
+def csr(succ):
+    return np.cumsum([0] + [len(x) for x in succ]).astype(np.int64), np.array([w for x in succ for w in x], np.int32)
+
+
+#: an op released by an op that another deferred op's run releases: op 11
+#: (9 -> 10 -> 11) is ready before op 7 on resource 0
+TWO_HOPS = (*csr([[1, 2], [3], [4], [8], [5], [6], [7], [], [9], [10], [11], []]),
+            np.array([0, 0, 1, 1, 2, 3, 4, 0, 1, 3, 4, 0], np.int32), 6)
+TWO_HOPS_DUR = np.array([[380, 268, 210, 22, 240, 416, 240, 381, 137, 83, 447, 305]], np.int32).T
+#: the same with edges between the hops
+TWO_HOPS_JOINED = (*csr([[1, 4], [5], [3, 6], [], [8], [9], [8], [8, 9], [10, 11, 14], [12, 16], [11], [], [13], [],
+                         [15, 16], [], []]),
+                   np.array([0, 0, 1, 1, 2, 2, 4, 4, 6, 6, 3, 0, 3, 0, 5, 1, 5], np.int32), 7)
+
+
+def test_deferred_op_released_by_a_released_one():
+    check(*TWO_HOPS, TWO_HOPS_DUR)
+    rng = np.random.default_rng(0)
+    for g in (TWO_HOPS, TWO_HOPS_JOINED):
+        for hi in (3, 8, 500):
+            check(*g, W.random_durations(g[2].size, 100, 1, hi, rng))
+
+
+@pytest.mark.parametrize("hops,extra,seed", [(3, False, 0), (3, False, 1), (1, True, 2), (3, True, 3)])
+def test_worker_graphs_with_hops(hops, extra, seed):
+    rng = np.random.default_rng(seed)
+    seen = collections.Counter()
+    for it in range(4000):
+        ptr, idx, res, R = ps_graph(rng, hops, extra)
+        dur = W.random_durations(res.size, 4, 1, (3, 8, 500)[it % 3], rng)
+        gap = rng.integers(0, 4, R).astype(np.int32) if it % 4 == 1 else None
+        delay = rng.integers(0, 6, R).astype(np.int32) if it % 5 == 1 else None
+        seen.update(set(check(ptr, idx, res, R, dur, gap=gap, delay=delay)))
+    assert all(seen[k] for k in (VISIT, RELEASE, LOAD, FORCE)), seen
