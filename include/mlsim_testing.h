@@ -93,15 +93,18 @@ int sim_testing_join_slots(int32_t n_ops, int32_t n_res, const int64_t *succ_ptr
  * The merge program the library builds for a graph, on the host only, so that
  * a test can interpret it and compare the result with an independent replay.
  * The graph arguments are those of sim_graph_create; device_model: the program
- * of calls with gaps or delays.  Outputs (host): head: {instructions, deferred entries, deferred chains, slots, first slot of the
- * chains' ready times, zero slot, infinity slot, slot nobody reads, 0, 1}, or
- * ten zeros when the graph has no program; then, when the arrays are large
- * enough (else SIM_E_LIMIT), ins [][13]: {kind, row, resource, out slot, four
- * operand slots, first chain of the cluster, one past its last, deferred
- * index, id, 1 when the ready time is the resource's free time} with kind 0 visit, 1 max, 2 release, 3 load, 4 force, 5 drain;
- * def [][4]: {row, id, chain, partner (the deferred index it releases when it
- * runs, whose duration a load hands over; -1: none)}; chain
- * [][2]: {first deferred index, resource}.  Ids are ranks of (priority, id).
+ * of calls with gaps or delays.  Outputs (host): head: {instructions, deferred
+ * entries, deferred chains, slots, first slot of the chains' ready times, zero
+ * slot, infinity slot, slot nobody reads, 0, 1}, or ten zeros when the graph
+ * has no program; then, when the arrays are large enough (else SIM_E_LIMIT),
+ * ins [][13]: {kind, row, resource, out slot, four operand slots, first chain
+ * of the cluster, one past its last, deferred index, id, 1 when the ready time
+ * is the resource's free time} with kind 0 visit, 1 max, 2 release, 3 load,
+ * 4 force, 5 drain; def [][4]: {row, id, chain, partner (the deferred index it
+ * releases when it runs, whose duration a load hands over; -1: none)}; chain
+ * [][4]: {first deferred index, resource, chain of its ops' partners, place by
+ * place (-1: none), chain whose partners its ops are (-1: none)}.  Ids are
+ * ranks of (priority, id).
  * Returns SIM_OK or the argument errors of sim_graph_create.
  */
 int sim_testing_merge_program(int32_t n_ops, int32_t n_res, const int64_t *succ_ptr,

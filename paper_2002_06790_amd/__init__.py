@@ -181,13 +181,13 @@ def join_slots(succ_ptr, succ_idx, op_res, n_res: int, prio=None):
 def merge_program(succ_ptr, succ_idx, op_res, n_res: int, prio=None, device_model: bool = False):
     """The merge program the library builds for a graph, on the host only
     (sim_testing_merge_program), or None: ``(head, ins int32 [n, 13], def
-    int32 [m, 4], chain int32 [c, 2])`` as described there."""
+    int32 [m, 4], chain int32 [c, 4])`` as described there."""
     ptr, idx, res, pr = _host(succ_ptr, np.int64), _host(succ_idx, np.int32), _host(op_res, np.int32), _host(prio, np.int32)
     n = int(ptr.size - 1)
     if res.size != n or (pr is not None and pr.size != n):
         raise ValueError("op_res and prio need one entry per op")
     head = np.zeros(10, np.int32)
-    out = [np.zeros((0, k), np.int32) for k in (13, 4, 2)]
+    out = [np.zeros((0, k), np.int32) for k in (13, 4, 4)]
     for _ in range(2):  # sizes first, then the arrays
         rc = _load().sim_testing_merge_program(n, int(n_res), _hptr(ptr), _hptr(idx), _hptr(res), _hptr(pr),
                                                int(device_model), _hptr(head), *[x for a in out for x in (_hptr(a) if a.size else None, a.shape[0])])
@@ -197,7 +197,7 @@ def merge_program(succ_ptr, succ_idx, op_res, n_res: int, prio=None, device_mode
             return None
         if rc == SIM_OK and out[0].size:
             break
-        out = [np.zeros((int(head[i]), k), np.int32) for i, k in enumerate((13, 4, 2))]
+        out = [np.zeros((int(head[i]), k), np.int32) for i, k in enumerate((13, 4, 4))]
     return (head, *out)
 
 

@@ -1103,8 +1103,8 @@ extern "C" int sim_testing_merge_program(int32_t n_ops, int32_t n_res, const int
       def = std::copy(w, w + 4, def);
     }
     for (const MergeChain &c : P.chain) {
-      *chain++ = c.beg;
-      *chain++ = c.res;
+      const int32_t w[4] = {c.beg, c.res, c.follow, c.lead};
+      chain = std::copy(w, w + 4, chain);
     }
   } catch (const std::bad_alloc &) {
     return SIM_E_NOMEM;

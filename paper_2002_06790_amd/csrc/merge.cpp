@@ -353,10 +353,11 @@ bool build(const Builder &B, const std::vector<int32_t> &row_of, bool partners, 
     learn(v);
   };
   // hands over the ready times of chain c (of cluster k) that are known, but
-  // that no scenario-independent place fits
+  // that no scenario-independent place fits; in the chain's order
   auto release = [&](int32_t k, int c, bool any) {
     bool done = false;
-    for (int32_t z; (z = first_open(c)) >= 0 && all_known(z) && (any || !clear(k, z)); done = true) {
+    for (int32_t z; (z = first_open(c)) >= 0 && B.pos[z] == (int32_t)un[c] && all_known(z) && (any || !clear(k, z));
+         done = true) {
       defers[c] = 1;
       state[z] = kReleased;
       if (partner[z] >= 0) {
@@ -426,16 +427,20 @@ bool build(const Builder &B, const std::vector<int32_t> &row_of, bool partners, 
     P.cluster[k].end = (int32_t)P.chain.size();
     if (P.cluster[k].end > P.cluster[k].beg) emit(kMgDrain, -1, k);
   }
+  // a chain's ops release those of another place by place, or none of them does
   for (int32_t v = 0; v < n; ++v) {
     if (state[v] != kFollows) continue;
-    // the leader's chain and this one match place by place
-    MergeChain &C = P.chain[mchain[B.ch[leader[v]]]];
-    const int32_t d = mchain[B.ch[v]];
-    if ((C.follow >= 0 && C.follow != d) || dx[leader[v]] - C.beg != dx[v] - P.chain[d].beg || C.len != P.chain[d].len)
-      return false;
-    C.follow = d;
-    P.chain[d].lead = mchain[B.ch[leader[v]]];
     P.def[dx[leader[v]]].partner = dx[v];
+    P.chain[mchain[B.ch[leader[v]]]].follow = mchain[B.ch[v]];
+    P.chain[mchain[B.ch[v]]].lead = mchain[B.ch[leader[v]]];
+  }
+  for (const MergeChain &C : P.chain) {
+    if (C.lead >= 0 && &P.chain[P.chain[C.lead].follow] != &C) return false;
+    if (C.follow < 0) continue;
+    const MergeChain &D = P.chain[C.follow];
+    if (D.len != C.len) return false;
+    for (int32_t i = 0; i < C.len; ++i)
+      if (P.def[C.beg + i].partner != D.beg + i) return false;
   }
   for (MergeIns &I : P.ins) {
     if (I.kind == kMgRelease || I.kind == kMgLoad || I.kind == kMgForce) I.x = dx[I.id];

@@ -131,6 +131,49 @@ TWO_HOPS_JOINED = (*csr([[1, 4], [5], [3, 6], [], [8], [9], [8], [8, 9], [10, 11
                          [15, 16], [], []]),
                    np.array([0, 0, 1, 1, 2, 2, 4, 4, 6, 6, 3, 0, 3, 0, 5, 1, 5], np.int32), 7)
 
+def graph(ptr, idx, res, R):
+    return np.array(ptr, np.int64), np.array(idx, np.int32), np.array(res, np.int32), R
+
+
+#: deferred chains of which only some ops release an op of another chain, or
+#: only some are released by one
+PART_OF_A_CHAIN = {
+    "leaders": graph([0, 2, 2, 4, 6, 6, 7, 8, 10, 10, 11, 12, 13], [3, 6, 5, 8, 7, 11, 4, 2, 9, 11, 5, 1, 10],
+                     [0, 0, 2, 0, 0, 2, 1, 0, 0, 1, 2, 1], 5),
+    "followers": graph([0, 1, 4, 5, 5, 7, 10, 10, 10, 10, 10, 11, 11], [1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11],
+                       [1, 0, 0, 1, 0, 1, 0, 1, 0, 1, 1, 0], 2),
+    "order": graph([0, 5, 12, 15, 17, 23, 26, 30, 30, 33, 34, 36, 36, 37, 37, 37],
+                   [1, 4, 5, 6, 9, 2, 6, 7, 8, 10, 12, 13, 3, 5, 10, 5, 12, 5, 6, 7, 8, 11, 12, 10, 13, 14, 7, 9, 10, 11,
+                    9, 10, 11, 14, 11, 14, 13], [1, 1, 0, 1, 1, 0, 1, 0, 0, 0, 1, 0, 1, 1, 0], 2)}
+
+
+def stream_graph(rng):
+    """Mostly ops of one predecessor, a few places back, on random resources."""
+    n, R = int(rng.integers(4, 40)), int(rng.integers(2, 7))
+    e = set()
+    for v in range(1, n):
+        for _ in range(1 if rng.random() < 0.85 else int(rng.integers(0, 4))):
+            e.add((max(0, v - 1 - int(rng.integers(0, rng.integers(1, 9)))), v))
+    e = np.array(sorted(e), np.int64).reshape(-1, 2)
+    return graph(np.concatenate([[0], np.cumsum(np.bincount(e[:, 0], minlength=n))]), e[:, 1], rng.integers(0, R, n), R)
+
+
+def test_streams():
+    rng = np.random.default_rng(0)
+    seen = collections.Counter()
+    for it in range(6000):
+        g = stream_graph(rng)
+        seen.update(set(check(*g, W.random_durations(g[2].size, 4, 1, (3, 8, 500)[it % 3], rng))))
+    assert all(seen[k] for k in (VISIT, RELEASE, LOAD, FORCE)), seen
+
+
+@pytest.mark.parametrize("which", PART_OF_A_CHAIN)
+def test_partners_in_part_of_a_chain(which):
+    g = PART_OF_A_CHAIN[which]
+    rng = np.random.default_rng(0)
+    for hi in (3, 8, 500):
+        check(*g, W.random_durations(g[2].size, 100, 1, hi, rng))
+
 
 def test_deferred_op_released_by_a_released_one():
     check(*TWO_HOPS, TWO_HOPS_DUR)
