@@ -1611,9 +1611,10 @@ int plan_scratch(sim_graph *g) {
   if (getenv("MLSIM_VERBOSE"))  // diagnostics only
     fprintf(stderr,
             "[mlsim] n=%d R=%d J=%d (barriers %d) heap_cap=%d (stride %d, lds end %d) cp_slots=%d (mode %d) "
-            "ev_blocks=%d cp_blocks=%d sw_blocks=%d ev_lds=%zu scratch=%zu MB x %d sets\n",
+            "ev_blocks=%d mg_blocks=%d,%d,%d,%d cp_blocks=%d sw_blocks=%d ev_lds=%zu scratch=%zu MB x %d sets\n",
             G.n, G.R, G.J, g->n_barriers, G.heap_cap, P.ev_heap_stride, P.ev_heap_le, G.cp_slots, P.cp_mode,
-            P.ev_blocks, P.cp_blocks, P.sw_blocks, P.ev_lds_bytes, off >> 20, n_sets);
+            P.ev_blocks, P.mg_blocks[0], P.mg_blocks[1], P.mg_blocks[2], P.mg_blocks[3], P.cp_blocks, P.sw_blocks,
+            P.ev_lds_bytes, off >> 20, n_sets);
   return SIM_OK;
 }
 

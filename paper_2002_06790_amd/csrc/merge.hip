@@ -500,10 +500,12 @@ __global__ __launch_bounds__(kWave) void k_merge(MergeTable T, MgArgs a) {
 #pragma unroll 1
           for (; u0 < k; ++u0) {
             const uint32_t w1 = MG_FIELD(u0, 1), row = MG_FIELD(u0, 0);
-            if (__ballot(m <= rf)) {
+            const int c0 = (int)(w1 >> 8 & 0x7ffu), c1 = (int)(w1 >> 20);
+            // (without deferred chains m is kNever, which a free time that
+            // overflowed may equal)
+            if (c0 < c1 && __ballot(m <= rf)) {
               const uint32_t t = !DEV && (w1 & kMgNext) ? rf : operands(q, u0, w1);
-              if (__ballot(m <= t))
-                m = run((int)(w1 >> 8 & 0x7ffu), (int)(w1 >> 20), false, t, (int)(MG_FIELD(u0, 5) >> 16), 0, 0, r, rf);
+              if (__ballot(m <= t)) m = run(c0, c1, false, t, (int)(MG_FIELD(u0, 5) >> 16), 0, 0, r, rf);
             }
             const uint32_t fin = rf + (uint32_t)duration(dv[base + u0], row);
             rf = fin;

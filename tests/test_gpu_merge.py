@@ -8,7 +8,7 @@ import torch
 import oracle
 import paper_2002_06790_amd as mlsim
 from paper_2002_06790_amd import workloads as W
-from test_merge_program import ps_graph
+from test_merge_program import PART_OF_A_CHAIN, TWO_HOPS, TWO_HOPS_DUR, TWO_HOPS_JOINED, ps_graph, stream_graph
 
 pytestmark = pytest.mark.gpu
 
@@ -91,3 +91,49 @@ def test_flagged_scenarios():
         pmk, _, _ = g2.run(d, place=place)
         assert torch.equal(pmk, mk)
         assert torch.equal(g2.run(d)[0], mk)
+
+
+def test_free_time_that_wraps_to_all_ones():
+    """2^31 - 1 twice and 1: the free time of a resource without deferred ops
+    is then the value that stands for no waiting op."""
+    n = 12
+    ptr = np.minimum(np.arange(n + 1), n - 1).astype(np.int64)
+    idx, res = np.arange(1, n, dtype=np.int32), np.zeros(n, np.int32)
+    p = mlsim.merge_program(ptr, idx, res, 1)
+    assert p is not None and not len(p[3])
+    rng = np.random.default_rng(0)
+    dur = rng.integers(1, 1000, (n, 70)).astype(np.int32)
+    for s in range(0, 60, 3):  # the sum is 2^32 - 1 after op ``at``, at every place of the frames
+        at = 2 + s // 3 % (n - 2)
+        dur[:at + 1, s] = [*[1] * (at - 2), 2**31 - 1, 2**31 - 1 - (at - 2), 1]
+        assert dur[:at + 1, s].sum(dtype=np.int64) == 2**32 - 1
+    g = mlsim.Graph(ptr, idx, res, 1)
+    omk, ofin, ost = oracle.run_batch(ptr, idx, res, 1, dur)
+    mk, fin, st = g.run(torch.from_numpy(dur).cuda(), want_finish=True)
+    assert np.array_equal(mk.cpu().numpy(), omk) and np.array_equal(st.cpu().numpy(), ost)
+    assert np.array_equal(fin.cpu().numpy()[:, ost == 0], ofin[:, ost == 0])
+
+
+def test_deferred_op_released_by_a_released_one():
+    g = mlsim.Graph(*TWO_HOPS)
+    mk, fin, _ = g.run(torch.from_numpy(TWO_HOPS_DUR).cuda(), want_finish=True)
+    assert mk.item() == 2023 and fin[11].item() == 1642 and fin[7].item() == 2023
+    rng = np.random.default_rng(1)
+    for g in (TWO_HOPS, TWO_HOPS_JOINED, *PART_OF_A_CHAIN.values()):
+        run_all(*g, W.random_durations(g[2].size, 70, 1, 300, rng), None, rng)
+
+
+@pytest.mark.parametrize("seed", [0, 1])
+def test_irregular_graphs(seed):
+    """Worker graphs with several pull hops and edges added or dropped, and streams."""
+    rng = np.random.default_rng(seed)
+    built = 0
+    for it in range(150):
+        ptr, idx, res, R = stream_graph(rng) if it % 3 == 2 else ps_graph(rng, 3, it % 3 == 1)
+        p = mlsim.merge_program(ptr, idx, res, R)
+        if p is None or not len(p[3]) or (p[3][:, 2] < 0).all() and it % 2:
+            continue  # programs with deferred ops, every second of them with partners
+        built += 1
+        own = np.random.default_rng(it)
+        run_all(ptr, idx, res, R, W.random_durations(res.size, 100, 1, (4, 50, 5000)[it % 3], own), None, own)
+    assert built > 10
