@@ -33,8 +33,9 @@ enum {
   SIM_TEST_CP_GLOBAL = 5,     /* value 0/1: the max-plus sweeps' value slots in global scratch (1) even
                                  when LDS holds them (static-order replays created afterwards too) */
   SIM_TEST_RF_GLOBAL = 6,     /* value 0/1: the event kernel's resource times in global scratch (1) */
-  SIM_TEST_NO_MERGE = 8,      /* value 0/1: the event list (1) even when the graph has a merge program; pins
-                                 1, 3, 4 and 6 imply it */
+  SIM_TEST_MERGE = 8,         /* value 0: the event list even when the graph has a merge program (pins 1, 3,
+                                 4 and 6 imply it); 1: the program even where the event list is expected to
+                                 be faster; -1: auto */
   SIM_TEST_SHARE_KEY_ID = 7   /* value 0/1: the sharing replay's ready-op key words hold only the op id
                                  (1), as for graphs whose ids and resources do not fit 32 bits together */
 };
@@ -95,8 +96,8 @@ int sim_testing_join_slots(int32_t n_ops, int32_t n_res, const int64_t *succ_ptr
  * The graph arguments are those of sim_graph_create; device_model: the program
  * of calls with gaps or delays.  Outputs (host): head: {instructions, deferred
  * entries, deferred chains, slots, first slot of the chains' ready times, zero
- * slot, infinity slot, slot nobody reads, 0, 1}, or ten zeros when the graph
- * has no program; then, when the arrays are large enough (else SIM_E_LIMIT),
+ * slot, infinity slot, slot nobody reads, 1 when calls take it (0: the event
+ * list is expected to be faster), 1}, or ten zeros when the graph has no program; then, when the arrays are large enough (else SIM_E_LIMIT),
  * ins [][13]: {kind, row, resource, out slot, four operand slots, first chain
  * of the cluster, one past its last, deferred index, id, 1 when the ready time
  * is the resource's free time} with kind 0 visit, 1 max, 2 release, 3 load,

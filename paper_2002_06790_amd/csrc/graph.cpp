@@ -874,6 +874,7 @@ extern "C" int sim_graph_create(int32_t n_ops, int32_t n_res, const int64_t *suc
   const std::vector<CpRec> cp_plain(C.cp);
   link_maxplus(C.cp, C.cp_pred, C.cp_slots, C.cp_n);
   std::vector<int32_t> mg_ins, mg_ins_dev, mg_def, mg_chain;
+  g->mg_pays = C.has_merge && merge_pays(C.merge, n_ops);
   if (C.has_merge) {
     pack_merge(C.merge_dev, mg_ins_dev, mg_def, mg_chain, g->mg_dev);
     pack_merge(C.merge, mg_ins, mg_def, mg_chain, g->mg);
@@ -1014,9 +1015,9 @@ extern "C" int sim_testing_replan(sim_graph *g, int32_t what, int32_t value) {
       if (value < 0 || value > 1) return SIM_E_INVAL;
       v.rf_global = value;
       break;
-    case SIM_TEST_NO_MERGE:
-      if (value < 0 || value > 1) return SIM_E_INVAL;
-      v.no_merge = value;
+    case SIM_TEST_MERGE:
+      if (value < -1 || value > 1) return SIM_E_INVAL;
+      v.merge = value;
       break;
     case SIM_TEST_SHARE_KEY_ID:
       if (value < 0 || value > 1) return SIM_E_INVAL;
@@ -1089,7 +1090,7 @@ extern "C" int sim_testing_merge_program(int32_t n_ops, int32_t n_res, const int
     std::fill(head, head + 10, 0);
     if (!C.has_merge) return SIM_OK;
     const int32_t h[10] = {(int32_t)P.ins.size(), (int32_t)P.def.size(), (int32_t)P.chain.size(), P.slots, P.head_slot,
-                           P.zero_slot, P.inf_slot, P.sink_slot, 0, 1};
+                           P.zero_slot, P.inf_slot, P.sink_slot, merge_pays(P, n_ops), 1};
     std::copy(h, h + 10, head);
     if (h[0] > ins_cap || h[1] > def_cap || h[2] > chain_cap) return SIM_E_LIMIT;
     for (const MergeIns &I : P.ins) {

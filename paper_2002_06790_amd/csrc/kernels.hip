@@ -1636,9 +1636,10 @@ int launch_event_impl(const sim_graph *g, char *base, int64_t n_scen, const int3
                       bool has_delay = false, const EvScratch *ext = nullptr) {
   const ScratchPlan &P = g->plan;
   const Variant &V = g->var;
-  // the merge program where the graph has one and no test pins the event list
-  // (its row strides are 32-bit byte counts)
-  if (!place && !ext && ld_dur < (1 << 30) && ld_fin < (1 << 30) && P.mg_blocks[0] && !V.no_merge && V.ev_lds_groups < 0 && !V.ev_blocks_cap && V.ev_reg < 0 &&
+  // the merge program where the graph has one that is faster (merge_pays) and
+  // no test pins the event list (its row strides are 32-bit byte counts)
+  if (!place && !ext && ld_dur < (1 << 30) && ld_fin < (1 << 30) && P.mg_blocks[0] &&
+      (V.merge >= 0 ? V.merge : g->mg_pays) && V.ev_lds_groups < 0 && !V.ev_blocks_cap && V.ev_reg < 0 &&
       !V.rf_global)
     return launch_merge(g, base, n_scen, dur, ld_dur, makespan, finish, ld_fin, status, prev, gen, dev, has_gap,
                         has_delay, stream);

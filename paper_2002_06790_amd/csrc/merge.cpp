@@ -506,6 +506,27 @@ bool merge_slots(MergeProgram &P, int32_t R, bool device_model) {
   return s < kMergeMaxSlots;
 }
 
+// A deferred op of a cluster with three chains or more costs a search over
+// the chains' first ready times, about 0.55 us and 0.3 us a chain, which few
+// deferred ops hide: replays of 16384 scenarios by the program take 53 us where
+// the event list takes 36 (19 ops, 9 of them deferred in one cluster of 5
+// chains), 79 / 52 (23 ops, 12 in 7), 42 / 44 (24 ops, 7 in 3) and 50 / 77 (42
+// ops, 4 in 3).  On 172 measured graphs of 1 to 250 ops (each by the mean over
+// plain, device-model, generated and attribution calls) the faster one is taken
+// on all but 4, where the other gains up to 20 %; the program on every graph
+// would lose on 29, up to 1.54 times.  Deferred ops of one chain or two stay in
+// registers: graphs of only such clusters are faster by the program throughout,
+// from 1 to 12000 ops, 64 to 262144 scenarios and up to the 64 KB of LDS that a
+// block may take (4.8 / 17.6 ms on ResNet-50, 16 workers, 58 KB, 16384
+// scenarios; 9.8 / 21.9 ms at 65536).
+bool merge_pays(const MergeProgram &P, int32_t n) {
+  int64_t cost = 0;
+  for (const MergeCluster &k : P.cluster)
+    for (int32_t c = k.beg; c < k.end && k.end - k.beg > 2; ++c)
+      cost += (int64_t)P.chain[c].len * (8 + k.end - k.beg);
+  return cost < 4 * (int64_t)n;
+}
+
 bool build_merge(int32_t n, int32_t R, const std::vector<std::vector<int32_t>> &succ,
                  const std::vector<std::vector<int32_t>> &pred, const std::vector<int32_t> &res,
                  const std::vector<int32_t> &row_of, const std::vector<int32_t> &topo, MergeProgram &P) {

@@ -141,6 +141,10 @@ bool build_merge(int32_t n, int32_t R, const std::vector<std::vector<int32_t>> &
                  const std::vector<std::vector<int32_t>> &pred, const std::vector<int32_t> &res,
                  const std::vector<int32_t> &row_of, const std::vector<int32_t> &topo, MergeProgram &P);
 
+// Whether replays of a graph of n ops are expected to be faster by its program
+// than by the event list.
+bool merge_pays(const MergeProgram &P, int32_t n);
+
 // Device view of a compiled graph (plain pointers, passed by value).
 struct DevGraph {
   int32_t n, R, J, nsrc;  // n real ops (barriers follow them), J join state slots
@@ -239,7 +243,7 @@ struct Variant {
   int32_t ev_reg = -1;         // heap root's children in registers (0/1), -1: auto
   int32_t cp_global = 0;       // max-plus value slots in global scratch (1) even when LDS holds them
   int32_t rf_global = 0;       // resource times in global scratch (1) even when LDS holds them
-  int32_t no_merge = 0;        // the event list (1) even when the graph has a merge program
+  int32_t merge = -1;          // the merge program where the graph has one (0/1), -1: where it is faster
   int32_t share_key_id = 0;    // sharing replay: ready-op key words without the resource (1)
 };
 
@@ -300,6 +304,7 @@ struct sim_graph {
   int device;
   mlsim::DevGraph dg;
   mlsim::MergeTable mg, mg_dev;  // the merge program without and with a device model
+  int32_t mg_pays;               // the program is expected to beat the event list
   mlsim::ScratchPlan plan;
   mlsim::Variant var;
   void *dev_mem;          // one allocation holding every graph array

@@ -8,7 +8,8 @@ import torch
 import oracle
 import paper_2002_06790_amd as mlsim
 from paper_2002_06790_amd import workloads as W
-from test_merge_program import PART_OF_A_CHAIN, TWO_HOPS, TWO_HOPS_DUR, TWO_HOPS_JOINED, ps_graph, stream_graph
+from test_merge_program import (MANY_CHAINS, PART_OF_A_CHAIN, TWO_HOPS, TWO_HOPS_DUR, TWO_HOPS_JOINED,
+                                ps_graph, stream_graph)
 
 pytestmark = pytest.mark.gpu
 
@@ -16,6 +17,7 @@ pytestmark = pytest.mark.gpu
 def run_all(ptr, idx, res, R, dur, prio=None, rng=None):
     """Every call that may take the merge kernel, each equal to the oracle."""
     g = mlsim.Graph(ptr, idx, res, R, prio=prio)
+    g.pin_variant("merge", 1)  # also where the event list is faster
     d = torch.from_numpy(dur).cuda()
     S = dur.shape[1]
     gap, delay = (rng.integers(0, 9, R).astype(np.int32) for _ in range(2))
@@ -116,6 +118,7 @@ def test_free_time_that_wraps_to_all_ones():
 
 def test_deferred_op_released_by_a_released_one():
     g = mlsim.Graph(*TWO_HOPS)
+    g.pin_variant("merge", 1)
     mk, fin, _ = g.run(torch.from_numpy(TWO_HOPS_DUR).cuda(), want_finish=True)
     assert mk.item() == 2023 and fin[11].item() == 1642 and fin[7].item() == 2023
     rng = np.random.default_rng(1)
@@ -137,3 +140,20 @@ def test_irregular_graphs(seed):
         own = np.random.default_rng(it)
         run_all(ptr, idx, res, R, W.random_durations(res.size, 100, 1, (4, 50, 5000)[it % 3], own), None, own)
     assert built > 10
+
+
+def test_program_taken_or_not():
+    """The library's choice, the event list and the program on a graph whose
+    program costs more than the event list, and on one where it pays."""
+    rng = np.random.default_rng(0)
+    for graph, pays in ((MANY_CHAINS, 0), (TWO_HOPS, None), (PART_OF_A_CHAIN["followers"], None)):
+        ptr, idx, res, R = graph
+        p = mlsim.merge_program(*graph)
+        dur = W.random_durations(res.size, 200, 1, 60, rng)
+        omk, ofin, _ = oracle.run_batch(ptr, idx, res, R, dur)
+        assert pays is None or p[0][8] == pays
+        g = mlsim.Graph(*graph)
+        for merge in (-1, 0, 1, -1):
+            g.pin_variant("merge", merge)
+            mk, fin, _ = g.run(torch.from_numpy(dur).cuda(), want_finish=True)
+            assert np.array_equal(mk.cpu().numpy(), omk) and np.array_equal(fin.cpu().numpy(), ofin), merge

@@ -194,3 +194,28 @@ def test_worker_graphs_with_hops(hops, extra, seed):
         delay = rng.integers(0, 6, R).astype(np.int32) if it % 5 == 1 else None
         seen.update(set(check(ptr, idx, res, R, dur, gap=gap, delay=delay)))
     assert all(seen[k] for k in (VISIT, RELEASE, LOAD, FORCE)), seen
+
+
+#: 7 of 17 ops deferred in one cluster of six chains
+MANY_CHAINS = graph([0, 4, 6, 7, 7, 8, 8, 9, 10, 10, 10, 12, 13, 16, 19, 19, 19, 19],
+                    [1, 2, 4, 6, 3, 9, 5, 10, 7, 8, 11, 15, 14, 13, 14, 15, 14, 15, 16],
+                    [1, 3, 3, 3, 0, 2, 0, 2, 2, 4, 0, 2, 4, 0, 1, 0, 3], 5)
+
+
+def test_program_is_taken_where_it_pays():
+    """A deferred op of a cluster of c > 2 chains counts 8 + c against 4 per op."""
+    assert not mlsim.merge_program(*MANY_CHAINS)[0][8]
+    for w in (W.resnet50_ps(n_scen=64), W.bert_large_ps(n_scen=64)):
+        assert mlsim.merge_program(w.succ_ptr, w.succ_idx, w.op_res, w.n_res)[0][8]
+    rng = np.random.default_rng(3)
+    seen = collections.Counter()
+    for it in range(3000):
+        g = stream_graph(rng) if it % 2 else ps_graph(rng, 3, True)
+        p = mlsim.merge_program(*g)
+        if p is None:
+            continue
+        size = {c: c1 - c0 for c0, c1 in p[1][:, 8:10] for c in range(c0, c1)}
+        cost = sum(8 + size[c] for c in p[2][:, 2] if size[c] > 2)
+        assert p[0][8] == (cost < 4 * g[2].size)
+        seen[int(p[0][8]), cost > 0] += 1
+    assert len(seen) == 3, seen
