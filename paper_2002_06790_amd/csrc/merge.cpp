@@ -44,7 +44,7 @@ namespace {
 constexpr int kChainsPerRes = 4;   // more chains on one resource: no program
 constexpr int kChainsMax = 256;    // more chains in all: no program
 constexpr int kInsertScan = 64;    // places tried from a chain's end for one op
-constexpr int64_t kWorkMax = 64 << 20;  // steps of the program search
+constexpr int64_t kWorkMax = 64 << 20;  // steps of the search for the chains, and of that for the program
 
 struct Builder {
   int n, R;
@@ -53,6 +53,8 @@ struct Builder {
 
   // chains and the facts proved about arrivals
   int nch = 0, W = 0;                        // chains, row width of the tables below
+  bool late = false;                         // an op came before one placed earlier
+  int64_t work = 0;                          // table entries and predecessors looked at
   std::vector<std::vector<int32_t>> chain;   // ops in key order
   std::vector<std::vector<int32_t>> of_res;  // chains of each resource
   std::vector<int32_t> ch, pos;              // chain of an op, its place
@@ -72,18 +74,28 @@ struct Builder {
   void raise_all(int32_t *to, const int32_t *from) const {
     for (int c = 0; c < nch; ++c) raise(to[c], from[c]);
   }
-  void learn_ready(int v) {
+  // (fresh: v's rows are still empty)
+  void learn_ready(int v, bool fresh) {
     int32_t *r = &rdy[(size_t)row[v] * W];
     for (int32_t p : pred[v]) {
-      raise_all(r, &arr[(size_t)row[p] * W]);
+      const int32_t *a = &arr[(size_t)row[p] * W];
+      if (fresh)
+        std::copy_n(a, nch, r);
+      else
+        raise_all(r, a);
+      fresh = false;
       raise(r[ch[p]], p);
     }
   }
-  void learn_arrival(int v) {
+  void learn_arrival(int v, bool fresh) {
     int32_t *a = &arr[(size_t)row[v] * W];
-    raise_all(a, &rdy[(size_t)row[v] * W]);
+    if (fresh)
+      std::copy_n(&rdy[(size_t)row[v] * W], nch, a);
+    else
+      raise_all(a, &rdy[(size_t)row[v] * W]);
     if (pos[v] > 0) {
       const int32_t t = chain[ch[v]][pos[v] - 1];
+      if (pred[v].size() == 1 && pred[v][0] == t) return;  // known with the ready time
       raise_all(a, &arr[(size_t)row[t] * W]);
       raise(a[ch[t]], t);
     }
@@ -117,12 +129,14 @@ struct Builder {
         }
       }
       if (scan == 0) continue;
+      late = late || i + 1 < (int)C.size();
       C.insert(C.begin() + i + 1, v);
       ch[v] = c;
       for (int k = i + 1; k < (int)C.size(); ++k) pos[C[k]] = k;
       return true;
     }
-    if ((int)list.size() >= kChainsPerRes || nch >= W) return false;
+    if ((int)list.size() >= kChainsPerRes || nch >= kChainsMax) return false;
+    if (nch == W) widen();
     list.push_back(nch);
     chain.push_back({v});
     ch[v] = nch++;
@@ -130,9 +144,21 @@ struct Builder {
     return true;
   }
 
+  void widen() {  // rows of twice the width
+    for (std::vector<int32_t> *t : {&rdy, &arr}) {
+      const size_t rows = t->size() / W;
+      std::vector<int32_t> wide(rows * 2 * W, -1);
+      for (size_t i = 0; i < rows; ++i) std::copy_n(t->begin() + i * W, W, wide.begin() + i * 2 * W);
+      t->swap(wide);
+    }
+    W *= 2;
+  }
+
   bool chains(const std::vector<int32_t> &topo) {
-    W = std::min(kChainsMax, kChainsPerRes * R);
+    W = std::min(kChainsMax, 2 * R);  // (a device's own ops, and those that others release)
     nch = 0;
+    late = false;
+    work = 0;
     chain.clear();
     of_res.assign(R, {});
     ch.assign(n, -1);
@@ -147,13 +173,15 @@ struct Builder {
       row[v] = rows++;
       rdy.resize((size_t)rows * W, -1);
       arr.resize((size_t)rows * W, -1);
-      learn_ready(v);
-      if (!place(v)) return false;
-      learn_arrival(v);
+      learn_ready(v, true);
+      work += (int64_t)pred[v].size() * (nch + kInsertScan);
+      if (work > kWorkMax || !place(v)) return false;
+      learn_arrival(v, true);
     }
-    for (int32_t v : topo) {  // once more: ops inserted into a chain late
-      learn_ready(v);
-      learn_arrival(v);
+    for (int32_t v : topo) {  // once more where an op was inserted into a chain late
+      if (!late) break;
+      learn_ready(v, false);
+      learn_arrival(v, false);
     }
     return true;
   }
