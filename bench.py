@@ -467,15 +467,16 @@ def main():
             if k != args.config:
                 per_config[workloads.make_config(k).name] = config_line(k, args, torch, mlsim, workloads)
 
-    # HBM traffic measured by counters for this exact kernel source, if any
+    # HBM traffic measured by counters for these exact sources of the replay, if any
     traffic = None
     try:
         import hashlib
         prof = json.load(open(os.path.join(ROOT, "profiles", "traffic.json")))
-        src = open(os.path.join(ROOT, "paper_2002_06790_amd", "csrc", "kernels.hip"), "rb").read()
-        if (prof.get("kernels_sha256") == hashlib.sha256(src).hexdigest() and args.config == 4
+        src = b"".join(open(os.path.join(ROOT, "paper_2002_06790_amd", "csrc", f), "rb").read()
+                       for f in ("kernels.hip", "merge.hip", "merge.cpp"))
+        if (prof.get("sources_sha256") == hashlib.sha256(src).hexdigest() and args.config == 4
                 and S == 262144 and args.algo in ("event", "auto")):
-            traffic = prof["k_event"]["read_bytes"] + prof["k_event"]["write_bytes"]
+            traffic = prof["k_merge"]["read_bytes"] + prof["k_merge"]["write_bytes"]
     except (OSError, ValueError, KeyError):
         traffic = None
 

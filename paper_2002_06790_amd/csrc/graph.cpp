@@ -805,6 +805,43 @@ int check_graph_args(int32_t n_ops, int32_t n_res, const int64_t *succ_ptr, cons
   return SIM_OK;
 }
 
+// What the upload and the graph object take besides the compiled graph.
+struct HostTables {
+  std::vector<int32_t> ap_ptr, ap, row_res, orig_of;
+  std::vector<AtRec> at_rec;
+  std::vector<CpRec> cp_plain;
+  std::vector<int32_t> mg_ins, mg_ins_dev, mg_def, mg_chain;
+  MergeTable mg{}, mg_dev{};
+  int32_t mg_pays = 0;
+};
+
+void host_tables(int32_t n_ops, const int32_t *op_res, Compiled &C, HostTables &H) {
+  // attribution: predecessors by caller id (ascending; implied ones removed:
+  // they finish strictly before the op that implies them) and resources
+  H.row_res.assign(op_res, op_res + n_ops);
+  H.ap_ptr.assign(n_ops + 1, 0);
+  std::vector<std::vector<int32_t>> pl(n_ops);
+  for (int32_t c = 0; c < n_ops; ++c) {
+    H.orig_of.push_back(C.ops[c].orig);
+    for (int32_t k = C.pred_ptr[c]; k < C.pred_ptr[c + 1]; ++k) pl[C.ops[c].orig].push_back(C.ops[C.pred[k]].orig);
+  }
+  for (int32_t v = 0; v < n_ops; ++v) {
+    std::sort(pl[v].begin(), pl[v].end());
+    H.ap.insert(H.ap.end(), pl[v].begin(), pl[v].end());
+    H.ap_ptr[v + 1] = (int32_t)H.ap.size();
+    AtRec r{op_res[v], H.ap_ptr[v + 1] - H.ap_ptr[v], H.ap_ptr[v], {-1, -1, -1}, {0, 0}};
+    for (int e = 0; e < kAtInline && e < r.np; ++e) r.p[e] = H.ap[r.beg + e];
+    H.at_rec.push_back(r);
+  }
+  H.cp_plain = C.cp;
+  link_maxplus(C.cp, C.cp_pred, C.cp_slots, C.cp_n);
+  if (C.has_merge) {
+    H.mg_pays = merge_pays(C.merge, n_ops);
+    pack_merge(C.merge_dev, H.mg_ins_dev, H.mg_def, H.mg_chain, H.mg_dev);
+    pack_merge(C.merge, H.mg_ins, H.mg_def, H.mg_chain, H.mg);
+  }
+}
+
 }  // namespace
 
 extern "C" int sim_graph_create(int32_t n_ops, int32_t n_res, const int64_t *succ_ptr,
@@ -814,9 +851,11 @@ extern "C" int sim_graph_create(int32_t n_ops, int32_t n_res, const int64_t *suc
   *out = nullptr;
   if (int rc = check_graph_args(n_ops, n_res, succ_ptr, succ_idx, op_res)) return rc;
   Compiled C;
+  HostTables H;
   int rc;
   try {
     rc = compile(n_ops, n_res, succ_ptr, succ_idx, op_res, prio, C);
+    if (!rc) host_tables(n_ops, op_res, C, H);
   } catch (const std::bad_alloc &) {
     return SIM_E_NOMEM;
   }
@@ -852,35 +891,9 @@ extern "C" int sim_graph_create(int32_t n_ops, int32_t n_res, const int64_t *suc
          o_jinfo = take(bytes_of(C.jinfo)), o_evsrc = take(bytes_of(C.ev_src)),
          o_rec16 = take(bytes_of(C.ev_rec16)), o_lvl = take(bytes_of(C.lvl_of)),
          o_levend = take(bytes_of(C.levend));
-  // attribution: predecessors by caller id (ascending; implied ones removed:
-  // they finish strictly before the op that implies them) and resources
-  std::vector<int32_t> ap_ptr(n_ops + 1, 0), ap, row_res(op_res, op_res + n_ops);
-  {
-    std::vector<std::vector<int32_t>> pl(n_ops);
-    for (int32_t c = 0; c < n_ops; ++c)
-      for (int32_t k = C.pred_ptr[c]; k < C.pred_ptr[c + 1]; ++k) pl[C.ops[c].orig].push_back(C.ops[C.pred[k]].orig);
-    for (int32_t v = 0; v < n_ops; ++v) {
-      std::sort(pl[v].begin(), pl[v].end());
-      ap.insert(ap.end(), pl[v].begin(), pl[v].end());
-      ap_ptr[v + 1] = (int32_t)ap.size();
-    }
-  }
-  std::vector<AtRec> at_rec(n_ops);
-  for (int32_t v = 0; v < n_ops; ++v) {
-    AtRec r{op_res[v], ap_ptr[v + 1] - ap_ptr[v], ap_ptr[v], {-1, -1, -1}, {0, 0}};
-    for (int e = 0; e < kAtInline && e < r.np; ++e) r.p[e] = ap[r.beg + e];
-    at_rec[v] = r;
-  }
-  const std::vector<CpRec> cp_plain(C.cp);
-  link_maxplus(C.cp, C.cp_pred, C.cp_slots, C.cp_n);
-  std::vector<int32_t> mg_ins, mg_ins_dev, mg_def, mg_chain;
-  g->mg_pays = C.has_merge && merge_pays(C.merge, n_ops);
-  if (C.has_merge) {
-    pack_merge(C.merge_dev, mg_ins_dev, mg_def, mg_chain, g->mg_dev);
-    pack_merge(C.merge, mg_ins, mg_def, mg_chain, g->mg);
-  }
-  const size_t o_mgi = take(bytes_of(mg_ins)), o_mgv = take(bytes_of(mg_ins_dev)), o_mgd = take(bytes_of(mg_def)), o_mgc = take(bytes_of(mg_chain));
-  const size_t o_atr = take(bytes_of(at_rec)), o_ap = take(bytes_of(ap)), o_rres = take(bytes_of(row_res));
+  const size_t o_mgi = take(bytes_of(H.mg_ins)), o_mgv = take(bytes_of(H.mg_ins_dev)),
+               o_mgd = take(bytes_of(H.mg_def)), o_mgc = take(bytes_of(H.mg_chain));
+  const size_t o_atr = take(bytes_of(H.at_rec)), o_ap = take(bytes_of(H.ap)), o_rres = take(bytes_of(H.row_res));
   if (hipMalloc(&g->dev_mem, off ? off : 256) != hipSuccess) {
     delete g;
     return SIM_E_NOMEM;
@@ -891,20 +904,20 @@ extern "C" int sim_graph_create(int32_t n_ops, int32_t n_res, const int64_t *suc
   };
   bool ok = put(o_ops, C.ops.data(), bytes_of(C.ops)) && put(o_succ, C.succ.data(), bytes_of(C.succ)) &&
             put(o_jneed, C.jneed.data(), bytes_of(C.jneed)) && put(o_src, C.src.data(), bytes_of(C.src)) &&
-            put(o_cp, C.cp.data(), bytes_of(C.cp)) && put(o_cpl, cp_plain.data(), bytes_of(cp_plain)) &&
+            put(o_cp, C.cp.data(), bytes_of(C.cp)) && put(o_cpl, H.cp_plain.data(), bytes_of(H.cp_plain)) &&
             put(o_cpp, C.cp_pred.data(), bytes_of(C.cp_pred)) &&
             put(o_pp, C.pred_ptr.data(), bytes_of(C.pred_ptr)) && put(o_pr, C.pred.data(), bytes_of(C.pred)) &&
             put(o_topo, C.topo.data(), bytes_of(C.topo)) &&
             put(o_wpp, C.wp_ptr.data(), bytes_of(C.wp_ptr)) && put(o_wp, C.wp.data(), bytes_of(C.wp)) &&
             put(o_wsp, C.ws_ptr.data(), bytes_of(C.ws_ptr)) && put(o_ws, C.ws.data(), bytes_of(C.ws)) &&
-            put(o_atr, at_rec.data(), bytes_of(at_rec)) && put(o_ap, ap.data(), bytes_of(ap)) &&
-            put(o_rres, row_res.data(), bytes_of(row_res)) &&
+            put(o_atr, H.at_rec.data(), bytes_of(H.at_rec)) && put(o_ap, H.ap.data(), bytes_of(H.ap)) &&
+            put(o_rres, H.row_res.data(), bytes_of(H.row_res)) &&
             put(o_evops, C.ev_ops.data(), bytes_of(C.ev_ops)) && put(o_evsucc, C.ev_succ.data(), bytes_of(C.ev_succ)) &&
             put(o_jinfo, C.jinfo.data(), bytes_of(C.jinfo)) && put(o_evsrc, C.ev_src.data(), bytes_of(C.ev_src)) &&
             put(o_rec16, C.ev_rec16.data(), bytes_of(C.ev_rec16)) &&
-            put(o_mgi, mg_ins.data(), bytes_of(mg_ins)) &&
-            put(o_mgv, mg_ins_dev.data(), bytes_of(mg_ins_dev)) && put(o_mgd, mg_def.data(), bytes_of(mg_def)) &&
-            put(o_mgc, mg_chain.data(), bytes_of(mg_chain)) &&
+            put(o_mgi, H.mg_ins.data(), bytes_of(H.mg_ins)) &&
+            put(o_mgv, H.mg_ins_dev.data(), bytes_of(H.mg_ins_dev)) && put(o_mgd, H.mg_def.data(), bytes_of(H.mg_def)) &&
+            put(o_mgc, H.mg_chain.data(), bytes_of(H.mg_chain)) &&
             put(o_lvl, C.lvl_of.data(), bytes_of(C.lvl_of)) && put(o_levend, C.levend.data(), bytes_of(C.levend));
   if (!ok) {
     (void)hipFree(g->dev_mem);
@@ -954,6 +967,9 @@ extern "C" int sim_graph_create(int32_t n_ops, int32_t n_res, const int64_t *suc
   d.levend = (const int32_t *)(base + o_levend);
   d.n_levels = C.levels;
 
+  g->mg = H.mg;
+  g->mg_dev = H.mg_dev;
+  g->mg_pays = H.mg_pays;
   for (MergeTable *t : {&g->mg, &g->mg_dev}) {
     t->R = n_res;
     t->ins = (const int32_t *)(base + (t == &g->mg ? o_mgi : o_mgv));
@@ -961,14 +977,13 @@ extern "C" int sim_graph_create(int32_t n_ops, int32_t n_res, const int64_t *suc
     t->chain = (const int32_t *)(base + o_mgc);
   }
 
-  g->h_orig_of.resize(n_ops);
-  for (int32_t c = 0; c < n_ops; ++c) g->h_orig_of[c] = C.ops[c].orig;
+  g->h_orig_of.swap(H.orig_of);
   g->n_barriers = C.barriers;
   g->row_identity = 1;
   for (int32_t c = 0; c < n_ops && g->row_identity; ++c) g->row_identity = C.ops[c].orig == c;
-  g->h_pred_ptr = C.pred_ptr;
-  g->h_pred = C.pred;
-  g->h_res.assign(op_res, op_res + n_ops);
+  g->h_pred_ptr.swap(C.pred_ptr);
+  g->h_pred.swap(C.pred);
+  g->h_res.swap(H.row_res);
 
   rc = plan_scratch(g);
   if (!rc) rc = plan_share(g);

@@ -185,6 +185,19 @@ def test_attr_walks(mlsim, S, R, placed):
     check_attr(mlsim, ptr, idx, res, R, dur, place=place, path_scen=S - 1)
 
 
+@pytest.mark.parametrize("R", [64, 123, 124, 125, 128, 129])
+def test_attr_accumulators_up_to_the_lds_limit(mlsim, R):
+    """Resource counts on both sides of the line where four wavefronts' block
+    would need more than 64 KB of LDS, and of the one where one's does."""
+    rng = np.random.default_rng(R)
+    n = 3 * R
+    ptr, idx, _, _ = W.random_dag(n, R, 2.0 / n, rng)
+    res = np.arange(n, dtype=np.int32) % R
+    dur = W.random_durations(n, 100, 1, 50, rng)
+    check_attr(mlsim, ptr, idx, res, R, dur, path_scen=5)
+    check_attr(mlsim, ptr, idx, res, R, dur, place=rng.integers(R, size=dur.shape).astype(np.uint16))
+
+
 def test_attr_status_and_empty(mlsim):
     ptr = np.array([0, 1, 2, 2], np.int64)
     idx = np.array([1, 2], np.int32)

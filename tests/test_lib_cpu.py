@@ -4,9 +4,12 @@ import glob
 import math
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
+import torch
 
 import paper_2002_06790_amd as mlsim
 
@@ -152,3 +155,62 @@ def test_no_environment_variable_selects_library_behaviour():
 def test_algorithm_three_is_invalid(L):
     # the value that once selected a removed algorithm is rejected before any GPU work
     assert L.sim_run_batch(None, 1, None, 1, None, 0, None, None, 0, None, 3, None) == mlsim.SIM_E_INVAL
+
+
+FAILING_NEW = """
+#include <cstdlib>
+#include <new>
+static long left = -1;
+extern "C" void fail_after(long k) { left = k; }
+extern "C" long failed() { return left < 0; }
+void *operator new(size_t n) {
+  if (left >= 0 && left-- == 0) throw std::bad_alloc();
+  void *p = std::malloc(n ? n : 1);
+  if (!p) throw std::bad_alloc();
+  return p;
+}
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, size_t) noexcept { std::free(p); }
+"""
+
+CHILD = """
+import ctypes, sys
+new, lib = ctypes.CDLL(sys.argv[1]), ctypes.CDLL(sys.argv[2])
+succ = [[1, 2], [3], [4], [8], [5], [6], [7], [], [9], [10], [11], []]
+ptr = (ctypes.c_int64 * 13)(*[sum(len(x) for x in succ[:k]) for k in range(13)])
+idx = (ctypes.c_int32 * 12)(*[w for x in succ for w in x])
+res = (ctypes.c_int32 * 12)(0, 0, 1, 1, 2, 3, 4, 0, 1, 3, 4, 0)
+def create():
+    h = ctypes.c_void_p()
+    rc = lib.sim_graph_create(12, 6, ptr, idx, res, None, ctypes.byref(h))
+    if rc == 0:
+        lib.sim_graph_destroy(h)
+    return rc
+end = create()  # without a GPU the first HIP call fails, after everything the host builds
+seen = 0
+for k in range(100000):
+    new.fail_after(ctypes.c_long(k))
+    rc = create()
+    done = not new.failed()
+    new.fail_after(ctypes.c_long(-1))
+    if done:
+        break
+    assert rc == -4 or rc == end, (k, rc)  # (the last ones are the HIP runtime's own)
+    seen += rc == -4
+print(end, seen)
+"""
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="stops at the first HIP call, which must fail")
+def test_create_reports_failed_allocations(tmp_path):
+    """Every allocation of the host side of sim_graph_create failing once:
+    SIM_E_NOMEM, no exception through the C boundary."""
+    src, so = tmp_path / "failing_new.cpp", tmp_path / "libfailing_new.so"
+    src.write_text(FAILING_NEW)
+    subprocess.check_call(["g++", "-O1", "-shared", "-fPIC", str(src), "-o", str(so)])
+    pre = os.environ.get("LD_PRELOAD")
+    env = {**os.environ, "LD_PRELOAD": f"{so}:{pre}" if pre else str(so)}
+    out = subprocess.run([sys.executable, "-c", CHILD, str(so), mlsim.LIB_PATH], env=env, capture_output=True, text=True)
+    assert out.returncode == 0, out.stderr[-2000:]
+    end, seen = map(int, out.stdout.split()[-2:])
+    assert end == mlsim.SIM_E_HIP and seen > 100
