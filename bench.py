@@ -531,9 +531,10 @@ def main():
                      "traffic_unit": "HBM bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, scaled)",
                      "kernel": "k_merge (sim_run_batch)",
                      "bytes_per_launch": alg_bytes,
-                     "limiter": "the instruction stream of at most four wavefronts per SIMD, and the deferred "
-                                "ops, whose accesses differ between lanes; the roofline axis is HBM bytes, which "
-                                "the kernel does not reach"},
+                     "limiter": "the instruction stream of one wavefront per SIMD (1024 blocks of 64 scenarios at "
+                                "a time): it issues in 45% of its cycles and waits in 50% (SQ counters, "
+                                "profiles/); the roofline axis is HBM bytes, of which the counters see 1.18 "
+                                "times the algorithmic ones"},
         "cpu_baseline": cpu,
         "parity": parity,
         "per_config": per_config,

@@ -86,7 +86,8 @@ enum {
  * not a valid value) */
 enum {
   SIM_ALGO_AUTO = 0,  /* library's choice (currently EVENT) */
-  SIM_ALGO_EVENT = 1, /* event-driven list scheduling, one scenario per lane */
+  SIM_ALGO_EVENT = 1, /* event-driven list scheduling, one scenario per lane; where most ops run in
+                         one order in every scenario, an instruction list made with the graph */
   SIM_ALGO_SWEEP = 2  /* level-synchronous conservative sweeps */
 };
 

@@ -1944,8 +1944,9 @@ int launch_cp(const sim_graph *g, char *scr, int64_t n_scen, const int32_t *dur,
               const DurGen *gen) {
   const ScratchPlan &P = g->plan;
   // Up to three wavefronts per SIMD the sweep that reads ahead in the linked
-  // table is faster; with four it is bound by the duration rows, and the other
-  // one streams them a little faster.  BERT-Large (16 workers), reading ahead /
+  // table is faster; with four the duration rows come in at 5.0 TB/s, near the
+  // 5.6 TB/s of a plain column maximum over as many rows, and the other one
+  // streams them a little faster.  BERT-Large (16 workers), reading ahead /
   // not: 779 / 906 us at 65536 scenarios, 900 / 970 at 131072, 1105 / 1138 at
   // 196608, 1470 / 1370 to 1440 at 262144.  With durations generated it is
   // always the faster one (4.84 / 4.89 ms at 262144).
@@ -1973,7 +1974,8 @@ int launch_attr(const sim_graph *g, char *scr, int64_t n_scen, const int32_t *du
   // not taken costs more than it hides.  Measured, k_attr_quad against k_attr:
   // ResNet-50 (8 workers) 0.87 / 1.67 ms at 16384 scenarios, 1.84 / 2.12 at
   // 65536; BERT-Large (16 workers) 2.48 / 2.32 ms at 65536, 8.6 / 6.2 at
-  // 200000; a random graph on 64 devices 2.4 / 5.4 ms at 8192.
+  // 200000; a random graph on 64 devices 2.4 / 5.4 ms at 8192.  Beside the
+  // accumulators (64 KB at most) a block of four holds 2 KB; a CU has 160 KB.
   const bool quad = tiles <= P.at_quad_tiles;
   using AtKernel = void (*)(DevGraph, AtArgs);
   const AtKernel kernel = P.at_lds ? (quad ? (place ? k_attr_quad<true, true> : k_attr_quad<false, true>)

@@ -25,7 +25,8 @@
 // for which that can be proved is visited; one for which it cannot is
 // deferred: a release instruction hands over its ready time once its
 // predecessors' arrivals are known to the program, unless it is the partner of
-// a deferred op (its one predecessor), whose run releases it.  A force
+// a deferred op (its one predecessor), whose run releases it (a chain's ops
+// release those of another chain place by place, all of them or none).  A force
 // instruction runs a cluster's deferred ops up to one of them in every
 // scenario, so that its arrival is known to the program.  The builder emits an
 // instruction only when its condition is proved, and gives up (the replay
