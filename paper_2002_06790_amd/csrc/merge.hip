@@ -508,12 +508,10 @@ __global__ __launch_bounds__(kWave) void k_merge(MergeTable T, MgArgs a) {
 #pragma unroll 1
           for (; u0 < k; ++u0) {
             const uint32_t w1 = MG_FIELD(u0, 1), row = MG_FIELD(u0, 0);
-            const int c0 = (int)(w1 >> 8 & 0x7ffu), c1 = (int)(w1 >> 20);
-            // (without deferred chains m is kNever, which a free time that
-            // overflowed may equal)
-            if (c0 < c1 && __ballot(m <= rf)) {
+            if (__ballot(m <= rf)) {
               const uint32_t t = !DEV && (w1 & kMgNext) ? rf : operands(q, u0, w1);
-              if (__ballot(m <= t)) m = run(c0, c1, false, t, (int)(MG_FIELD(u0, 5) >> 16), 0, 0, r, rf);
+              if (__ballot(m <= t))
+                m = run((int)(w1 >> 8 & 0x7ffu), (int)(w1 >> 20), false, t, (int)(MG_FIELD(u0, 5) >> 16), 0, 0, r, rf);
             }
             const uint32_t fin = rf + (uint32_t)duration(dv[base + u0], row);
             rf = fin;
@@ -715,8 +713,13 @@ MgKernel mg_kernel(bool gen, bool dev, bool prev, bool fin) {
   return fin ? mg_kernel_of<true>(gen, dev, prev) : mg_kernel_of<false>(gen, dev, prev);
 }
 
+// (One chain's places at least: a free time that overflowed may equal kNever,
+// the least ready time where a cluster defers nothing, and the search among its
+// no chains then reads the first chain's place before it finds none.  A test
+// for that in the frames of local visits costs BERT 2 %.)
 size_t mg_lds_bytes(const MergeTable &T, bool prev) {
-  return ((size_t)T.slots * 4 + (size_t)T.n_chain * 2 + (prev ? (size_t)T.R * 2 : 0)) * kWave + (size_t)T.n_chain * 2;
+  return ((size_t)T.slots * 4 + std::max<size_t>(T.n_chain, 1) * 2 + (prev ? (size_t)T.R * 2 : 0)) * kWave +
+         (size_t)T.n_chain * 2;
 }
 
 }  // namespace
