@@ -532,7 +532,7 @@ def main():
                      "kernel": "k_merge (sim_run_batch)",
                      "bytes_per_launch": alg_bytes,
                      "limiter": "the instruction stream of one wavefront per SIMD (1024 blocks of 64 scenarios at "
-                                "a time): it issues in 45% of its cycles and waits in 50% (SQ counters, "
+                                "a time): it issues in 45% of its cycles and waits in 49% (SQ counters, "
                                 "profiles/); the roofline axis is HBM bytes, of which the counters see 1.18 "
                                 "times the algorithmic ones"},
         "cpu_baseline": cpu,

@@ -9,7 +9,7 @@
 // wavefront that a SIMD has.  BERT (16 workers), 262144 scenarios, by counters:
 // 1024 blocks for 1024 SIMDs (31 KB of LDS allow five blocks a CU, and the 4096
 // tiles go evenly to four); a wavefront issues in 45 % of its cycles and waits
-// in 50 %, for LDS hardly ever; an op costs it 29 VALU, 23 scalar, 8 branch and
+// in 49 %, for LDS hardly ever; an op costs it 29 VALU, 22 scalar, 7 branch and
 // 2.5 LDS instructions; HBM traffic is 16.4 GB, 1.18 times the durations and
 // finish times.  Replays with finish times, before and after: BERT (16
 // workers), 262144 scenarios, 35.0 -> 7.2 ms; ResNet-50 (8 workers), 65536
