@@ -146,13 +146,14 @@ struct Builder {
   }
 
   void widen() {  // rows of twice the width
+    const int wide = std::min(2 * W, kChainsMax);
     for (std::vector<int32_t> *t : {&rdy, &arr}) {
       const size_t rows = t->size() / W;
-      std::vector<int32_t> wide(rows * 2 * W, -1);
-      for (size_t i = 0; i < rows; ++i) std::copy_n(t->begin() + i * W, W, wide.begin() + i * 2 * W);
-      t->swap(wide);
+      std::vector<int32_t> x(rows * wide, -1);
+      for (size_t i = 0; i < rows; ++i) std::copy_n(t->begin() + i * W, W, x.begin() + i * wide);
+      t->swap(x);
     }
-    W *= 2;
+    W = wide;
   }
 
   bool chains(const std::vector<int32_t> &topo) {
